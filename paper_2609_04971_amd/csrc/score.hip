@@ -245,14 +245,16 @@ struct alignas(16) Smem {
     int nact;
 };
 
-// Occupied beacon slots of head h, ascending, into act / *nact.
+// Occupied beacon slots of head h, ascending, into act / *nact.  One load
+// per lane and a ballot: walked one after the other by one thread, 64 slots
+// were 64 dependent loads.
 __device__ __forceinline__ void active_slots(const Args& a, int h, int* act, int* nact) {
-    if (threadIdx.x == 0) {
-        const int32_t* cnt = a.counts + (size_t)h * a.C;  // not read when C == 0
-        int n = 0;
-        for (int c = 0; c < a.C; ++c)
-            if (cnt[c] > 0) act[n++] = c;
-        *nact = n;
+    if (threadIdx.x < 64) {  // the first wave; C <= 64
+        const int c = threadIdx.x;
+        const bool occupied = c < a.C && a.counts[(size_t)h * a.C + c] > 0;
+        const unsigned long long m = __ballot(occupied);
+        if (occupied) act[__popcll(m & ((1ull << c) - 1))] = c;
+        if (c == 0) *nact = __popcll(m);
     }
     __syncthreads();
 }
@@ -710,31 +712,62 @@ __device__ __forceinline__ void wait_vmem() {
 // Rows of head h into the workspace: row tile rt, vector v, lane l holds the
 // 16 bytes lane l presents to the MFMA, i.e. chunk 4 v + l / 16 of row
 // 16 rt + l % 16; plus the head's occupied-slot list.
+//
+// One wave per row tile, four tiles per workgroup, and every lane forms its
+// vectors from the inputs by itself: a chain of two memory round trips (the
+// slots' counts, then the row).  Bound by those two trips on small layers
+// and by the rows' bytes on large ones.  Staging up to 144 rows through LDS
+// in one workgroup per head, with the slot list walked by one thread, took
+// 9 to 30 us per layer and 99 us for 4608 heads of 144 rows (170 MB written).
+constexpr int kRowTilesPerBlock = kWaves;
+
 template <int D>
 __global__ __launch_bounds__(kThreads) void rows_kernel(Args a) {
-    constexpr int LD = D + 8, NV = Op<uint16_t, D>::NV;
-    __shared__ uint16_t y[kFRT * 16 * LD];
+    constexpr int NV = Op<uint16_t, D>::NV, H = D / 2;
     __shared__ int act[kMaxC];
-    __shared__ int nact;
-    const int h = blockIdx.x, tid = threadIdx.x;
-    reset_head_control(a, h);
-    active_slots(a, h, act, &nact);
-    // up to 144 rows at a time through LDS
-    for (int r0 = 0; r0 < a.R_pad_max; r0 += kFRT * 16) {
-        const int nr = min(kFRT * 16, a.R_pad_max - r0);
-        build_rows<uint16_t, D, LD>(a, h, r0, nr, act, nact, y);
-        __syncthreads();
-        dev::u32x4* out = reinterpret_cast<dev::u32x4*>(a.rows) + ((size_t)h * a.R_pad_max + r0) * D / 8;
-        const int n = nr / 16 * NV * 64;
-        for (int i = tid; i < n; i += kThreads) {
-            const int lane = i & 63, v = (i >> 6) % NV, rt = (i >> 6) / NV;
-            out[i] = *reinterpret_cast<const dev::u32x4*>(y + (rt * 16 + (lane & 15)) * LD + (4 * v + (lane >> 4)) * 8);
-        }
-        __syncthreads();
+    __shared__ int nact_s;
+    const int h = blockIdx.x, lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
+    if (blockIdx.y == 0) reset_head_control(a, h);
+    active_slots(a, h, act, &nact_s);
+    const int nact = nact_s, R = nact + a.G * a.W;
+    if (blockIdx.y == 0) {
+        int* meta = a.rmeta + (size_t)h * kMetaWords;
+        if (threadIdx.x == 0) meta[0] = nact;
+        for (int c = threadIdx.x; c < nact; c += kThreads) meta[kMetaAct + c] = act[c];
     }
-    int* meta = a.rmeta + (size_t)h * kMetaWords;
-    if (tid == 0) meta[0] = nact;
-    for (int c = tid; c < nact; c += kThreads) meta[kMetaAct + c] = act[c];
+    const int rt = blockIdx.y * kRowTilesPerBlock + (threadIdx.x >> 6);
+    if (rt * 16 >= a.R_pad_max) return;
+    const int r = rt * 16 + c16;
+    dev::u32x4 val[NV];
+    if (r < nact) {  // an occupied beacon, rotated to the step and rounded
+        const float* beta = a.beacons + ((size_t)h * a.C + act[r]) * D;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const int e0 = 8 * (4 * v + g), i0 = e0 & (H - 1);  // elements e0 .. e0 + 7, pairs i0 .. i0 + 7
+#pragma unroll
+            for (int e = 0; e < 8; e += 2) {
+                uint16_t o[2];
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const int i = i0 + e + k;
+                    float2 p = make_float2(beta[i], beta[i + H]);
+                    if (a.rope_cos) p = rope_pair(p.x, p.y, a.rope_cos[i], a.rope_sin[i]);
+                    o[k] = dev::f32_to_bf16_rne(e0 < H ? p.x : p.y);
+                }
+                val[v][e / 2] = (unsigned)o[0] | ((unsigned)o[1] << 16);
+            }
+        }
+    } else {  // a recent query of the group, or padding
+        const int b = h / a.Hkv, kh = h % a.Hkv;
+        const uint16_t* q = reinterpret_cast<const uint16_t*>(a.qwin) +
+                            (((size_t)b * a.Hq + (size_t)kh * a.G) * a.W + (r - nact)) * D;
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+            val[v] = r < R ? *reinterpret_cast<const dev::u32x4*>(q + 8 * (4 * v + g)) : dev::u32x4{0u, 0u, 0u, 0u};
+    }
+    dev::u32x4* out = reinterpret_cast<dev::u32x4*>(a.rows) + ((size_t)h * a.R_pad_max + rt * 16) * D / 8 + lane;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) out[v * 64] = val[v];
 }
 
 // Row group rg (rows 16 RT rg .. 16 RT (rg + 1) - 1) of head h into registers.
@@ -1692,7 +1725,8 @@ __global__ __launch_bounds__(kThreads, 2) void evict_kernel(Args a) {
 
 template <int D, int RT>
 hipError_t launch_fast_rt(const Args& a, hipStream_t s) {
-    hipLaunchKernelGGL((rows_kernel<D>), dim3(a.P), dim3(kThreads), 0, s, a);
+    const int row_blocks = (a.R_pad_max / 16 + kRowTilesPerBlock - 1) / kRowTilesPerBlock;
+    hipLaunchKernelGGL((rows_kernel<D>), dim3(a.P, row_blocks), dim3(kThreads), 0, s, a);
     const bool multi = a.R_pad_max > RT * 16;
     // four row groups of 7 to 9 tiles (R of about 400 to 576): one per wave
     if constexpr (RT >= 7) {
