@@ -3,7 +3,7 @@
 // replaces a query buffer by its selection (Section 4.2, Eq. fps_q; the
 // FPS steps of Algorithm 2).
 //
-// One head per workgroup, three kernels by set size:
+// One head per workgroup, four kernels by set size:
 //
 //  - fps_gram_kernel, n <= 64, one wave.  These are the buffers of the
 //    continual path (B_Q^max = n_beacon + n_recent rows).  The whole Gram
@@ -14,14 +14,18 @@
 //  - fps_reg_kernel, bf16 and 64 < n <= 1024, 512 threads.  Prefill-sized
 //    sets held in MFMA operand registers: each pick is one MFMA pass over
 //    the head's rows against the picked row, and one barrier.
-//  - fps_stream_kernel, fp32 sets and bf16 sets past 1024 rows, n up to
-//    32768, 512 threads.  Thread t owns rows j = t + 512 i and keeps their
-//    S_j and 1/|q_j| in registers; each pick re-reads every row once to
-//    form cos(q_j, q_r), so the kernel moves about (m + 3) n D elements.
+//  - fps_lazy_kernel, sets of 1024 rows or more (bf16: more than 1024) whose
+//    per-row state fits LDS (about 16000 rows), at most 128 picks, 512
+//    threads.  Three passes over the rows; after the first pick a row is
+//    read again only when its S_j may be the lowest.
+//  - fps_stream_kernel, the other sets, n up to 32768, 512 threads.  Thread
+//    t owns rows j = t + 512 i and keeps their S_j and 1/|q_j| in registers;
+//    each pick re-reads every row once to form cos(q_j, q_r), so the kernel
+//    moves about (m + 3) n D elements.
 //
-// The two larger kernels use the regrouped average
+// The three larger kernels use the regrouped average
 //     sum_j cos(q_i, q_j) = (q_i / |q_i|) . sum_j (q_j / |q_j|),
-// which is O(n D) instead of O(n^2 D).  All three take the lowest index among equal values at every argmin, treat a
+// which is O(n D) instead of O(n^2 D).  All four take the lowest index among equal values at every argmin, treat a
 // zero vector as having cosine 0 with everything, and emit the picks in
 // selection order.  The 1/n of avg_i is left out: it does not move the
 // argmin.
@@ -157,6 +161,12 @@ __device__ __forceinline__ float wave_min(float v) {
     v = dpp_min<0x141>(v);  // row_half_mirror
     v = dpp_min<0x140>(v);  // row_mirror
     return fminf(fminf(lane_value(v, 0), lane_value(v, 16)), fminf(lane_value(v, 32), lane_value(v, 48)));
+}
+
+// The value of lane SEL of each quad (a quad_perm control: 0x00, 0x55, 0xaa, 0xff).
+template <int SEL>
+__device__ __forceinline__ float quad_lane(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), SEL, 0xf, 0xf, false));
 }
 
 // NB = ceil(n / 16) row blocks.  src is not restrict: dst may be src.
@@ -445,6 +455,331 @@ __global__ __launch_bounds__(kStreamThreads) void fps_stream_kernel(const T* src
     write_counts(counts, h, dst_rows, kmax, t, NT);
 }
 
+// ---- sets past the register kernel's: rows streamed three times, picks lazy ------
+//
+// A head takes one 512-thread workgroup.  Two passes over the rows give the
+// norms with the sum of unit vectors, then the averages (C21's regrouped
+// form) and the first pick, and a third gives every row's cosine with it.
+// From there on S_j is only brought up to date where it can matter: S_j
+// never falls as picks are added, so a value taken against the first t_j
+// picks is a lower bound, and a row whose bound lies above an exact value
+// cannot be the argmin.  Each wave owns a run of rows and repeats: find its
+// lowest bound; if that row is exact, or lies above the lowest exact value
+// any wave has found for this pick, the wave is done; else re-read the (up
+// to kBatch) rows of its lanes' lowest bounds and take them against the
+// picks they miss.  Every value is the one the eager rule forms, whatever
+// the order, so the picks are the same.  On queries around centroids the
+// first 15 of 16 picks' cosines cost about two passes over the rows instead
+// of 15: 512 heads of 4096 x 128 bf16 rows take @NEW@ us, 1750 when every
+// pick re-read every row.  Bound by the three passes (1.6 GB; a head's 1 MB
+// does not stay in its XCD's L2) and, per pick, by a few dependent reads.
+//
+// Rows are read by D * sizeof(T) / 16 lanes each, 16 bytes a lane (whole
+// lines, 1 KB per instruction); the vector a pass multiplies with sits in
+// registers, a chunk a lane.  K_j, the order key of S_j (the highest key
+// once picked), 1/|q_j| and t_j live in LDS: 9 bytes a row, and the picked
+// rows as they are, so the sets that fit (lazy_lds_bytes) go this way.
+constexpr int kLazyThreads = 512;
+constexpr int kLazyWaves = kLazyThreads / 64;
+constexpr int kLazyMaxPicks = 128;          // t_j is a byte and the picked rows stay in LDS
+constexpr size_t kLazyMaxLds = 160 * 1024 - 1024;
+constexpr unsigned kPicked = 0xffffffffu;   // above the key of every value
+
+// Sum over the LPR lanes of a row, the same in each of them.
+template <int LPR>
+__device__ __forceinline__ float row_lanes_sum(float v) {
+    v = dev::dpp_add<0x141>(dev::quad_sum(v));          // 8 lanes
+    if constexpr (LPR >= 16) v = dev::dpp_add<0x140>(v);  // 16
+    if constexpr (LPR >= 32) v += dev::shfl_xor_f(v, 16);
+    return v;
+}
+
+template <typename T, int D>
+struct Lazy {
+    static constexpr int EV = Elt<T>::EV, CPR = D * (int)sizeof(T) / 16, RPI = 64 / CPR;  // rows per load instruction
+    static constexpr int U = 4;         // load instructions of one step of a pass; the next step's are in flight too
+    static constexpr int LDP = CPR + 1;  // chunks between picked rows in LDS: 16 rows' chunks lie in distinct banks
+};
+constexpr int kBatch = 32;  // rows brought up to date at a time: two 16-row MFMA tiles
+
+// LDS: the picked rows, then per row the key, 1/|q| and t, then the head of
+// the block below.
+struct alignas(16) LazyHead {
+    float part[kLazyWaves][128];  // the waves' sums of unit vectors
+    float vec[128];
+    unsigned long long low[2];    // lowest exact (key, row) found for the current pick
+    unsigned long long post[kLazyWaves];
+    int list[kLazyWaves][kBatch];
+    int pick[kLazyMaxPicks];
+};
+
+template <typename T, int D>
+constexpr size_t lazy_lds_bytes(int n, int kmax) {
+    return sizeof(LazyHead) + (size_t)kmax * Lazy<T, D>::LDP * 16 + (size_t)((n + 15) / 16 * 16) * 9;
+}
+
+template <typename T, int D>
+__global__ __launch_bounds__(kLazyThreads, 4) void fps_lazy_kernel(const T* src, int src_rows, int n, int kmax,
+                                                                  int32_t* picks, void* dst, int widen, int dst_rows,
+                                                                  int32_t* counts) {
+    using Z = Lazy<T, D>;
+    constexpr int EV = Z::EV, LPR = Z::CPR, CPR = Z::CPR, RPI = Z::RPI, U = Z::U, LDP = Z::LDP;
+    constexpr int NV = Blk<T, D>::NV;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    LazyHead& sh = *reinterpret_cast<LazyHead*>(lds);
+    u32x4* prow = reinterpret_cast<u32x4*>(lds + sizeof(LazyHead));  // [kmax][LDP] picked rows
+    const int np = (n + 15) / 16 * 16;
+    unsigned* key = reinterpret_cast<unsigned*>(prow + (size_t)kmax * LDP);  // [np]
+    float* inv = reinterpret_cast<float*>(key + np);                        // [np]
+    unsigned char* seen = reinterpret_cast<unsigned char*>(inv + np);       // [np] picks in key
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int sub = lane / LPR, c = lane % LPR;  // row of a load instruction, 16-byte chunk of the row
+    const int h = blockIdx.x;
+    const T* qh = src + (size_t)h * src_rows * D;
+    // this wave's rows [j0, j1)
+    const int per = ((n + kLazyWaves - 1) / kLazyWaves + RPI - 1) / RPI * RPI;
+    const int j0 = min(wave * per, n), j1 = min(j0 + per, n);
+    auto fence = [] { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront"); };  // orders this wave's LDS accesses
+
+    // A pass: body(jb, x) for RPI * U rows of the wave at a time, lane (sub,
+    // c) holding chunk c of rows jb + u RPI + sub; the next step's rows are
+    // loaded before this one's body (rows past the wave's last read its last
+    // again, and are not stored).
+    auto pass = [&](bool down, auto&& body) {
+        constexpr int S = RPI * U;
+        const int ns = (j1 - j0 + S - 1) / S;
+        auto at = [&](int i) { return j0 + (down ? ns - 1 - i : i) * S; };
+        auto load = [&](u32x4* x, int jb) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int j = max(min(jb + u * RPI + sub, j1 - 1), j0);
+                x[u] = load16(qh + (size_t)j * D + c * EV);
+            }
+        };
+        if (ns == 0) return;
+        u32x4 x[U], y[U];
+        load(x, at(0));
+        for (int i = 0; i < ns; i += 2) {
+            load(y, at(i + 1));
+            body(at(i), x);
+            if (i + 1 >= ns) break;
+            load(x, at(i + 2));
+            body(at(i + 1), y);
+        }
+    };
+    // norms and the sum of unit vectors
+    {
+        float acc[EV];
+#pragma unroll
+        for (int e = 0; e < EV; ++e) acc[e] = 0.f;
+        pass(false, [&](int jb, const u32x4* x) {
+            float ss[U], iv[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                float f[EV], p = 0.f;
+                Elt<T>::unpack(x[u], f);
+#pragma unroll
+                for (int e = 0; e < EV; ++e) p = fmaf(f[e], f[e], p);
+                ss[u] = row_lanes_sum<LPR>(p);
+            }
+            // one reciprocal root for the four rows: lane u of each quad takes row u
+            const float mine = inv_norm((lane & 2) ? ((lane & 1) ? ss[3] : ss[2]) : ((lane & 1) ? ss[1] : ss[0]));
+            iv[0] = quad_lane<0x00>(mine);
+            iv[1] = quad_lane<0x55>(mine);
+            iv[2] = quad_lane<0xaa>(mine);
+            iv[3] = quad_lane<0xff>(mine);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int j = jb + u * RPI + sub;
+                const float w = j < j1 ? iv[u] : 0.f;
+                if (c == 0 && j < j1) inv[j] = w;
+                float f[EV];
+                Elt<T>::unpack(x[u], f);
+#pragma unroll
+                for (int e = 0; e < EV; ++e) acc[e] = fmaf(f[e], w, acc[e]);
+            }
+        });
+        // the wave's rows of one chunk lie LPR lanes apart
+#pragma unroll
+        for (int e = 0; e < EV; ++e) {
+#pragma unroll
+            for (int o = LPR; o < 64; o *= 2) acc[e] += dev::shfl_xor_f(acc[e], o);
+            if (lane < LPR) sh.part[wave][c * EV + e] = acc[e];
+        }
+        __syncthreads();
+        if (t < D) {
+            float s = 0.f;
+#pragma unroll
+            for (int w = 0; w < kLazyWaves; ++w) s += sh.part[w][t];
+            sh.vec[t] = s;
+        }
+        if (t < 2) sh.low[t] = ~0ull;
+        __syncthreads();
+    }
+    // key of scale * <q_j, v> / |q_j| for every row of the wave, v a chunk a lane
+    auto project = [&](bool down, const float* v, float scale, unsigned char mark) {
+        pass(down, [&](int jb, const u32x4* x) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                float f[EV], p = 0.f;
+                Elt<T>::unpack(x[u], f);
+#pragma unroll
+                for (int e = 0; e < EV; ++e) p = fmaf(f[e], v[e], p);
+                p = row_lanes_sum<LPR>(p);
+                const int j = jb + u * RPI + sub;
+                if (c == 0 && j < j1 && !(mark && key[j] == kPicked)) {
+                    key[j] = dev::ord_key(p * inv[j] * scale);
+                    seen[j] = mark;
+                }
+            }
+        });
+        fence();
+    };
+    {
+        float v[EV];
+#pragma unroll
+        for (int e = 0; e < EV; ++e) v[e] = sh.vec[c * EV + e];
+        fence();
+        project(true, v, 1.f, 0);  // the averages, times n
+    }
+
+    for (int k = 0; k < kmax; ++k) {
+        unsigned long long* low = &sh.low[k & 1];
+        unsigned long long mine = ~0ull;  // the wave's lowest exact (key, row), once it is known to be its lowest
+        for (;;) {
+            unsigned lk = kPicked;
+            int lj = j0;
+            for (int j = j0 + lane; j < j1; j += 64) {
+                const unsigned x = key[j];
+                if (x < lk) {
+                    lk = x;
+                    lj = j;
+                }
+            }
+            const unsigned wk = dev::wave_min_u32(lk);
+            if (wk == kPicked) break;  // every row picked (or no rows)
+            const int wj = (int)dev::wave_min_u32(lk == wk ? (unsigned)lj : ~0u);
+            const unsigned long long w = ((unsigned long long)wk << 32) | (unsigned)wj;
+            if (seen[wj] == k) {
+                mine = w;
+                if (lane == 0) atomicMin(low, w);
+                break;
+            }
+            // one 8-byte read, the same in every lane
+            const unsigned long long b = __hip_atomic_load(low, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            const unsigned long long bound =
+                ((unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)(b >> 32)) << 32) |
+                (unsigned)__builtin_amdgcn_readfirstlane((unsigned)b);
+            if (w > bound) break;
+            // the lanes whose lowest row is a bound below everything exact;
+            // narrowed to about a batch of the lowest
+            const bool cand = lk != kPicked && seen[lj] != k && (((unsigned long long)lk << 32) | (unsigned)lj) < bound;
+            unsigned long long m = __ballot(cand);
+            unsigned lo = wk, hi = kPicked;
+            for (int it = 0; it < 32 && __popcll(m) > kBatch; ++it) {
+                const unsigned mid = lo + (hi - lo) / 2;
+                const unsigned long long mm = __ballot(cand && lk <= mid);
+                if (mm == 0ull) {
+                    lo = mid;
+                } else {
+                    m = mm;
+                    hi = mid;
+                }
+            }
+            const int rank = __popcll(m & ((1ull << lane) - 1));
+            const int cnt = min((int)__popcll(m), kBatch);
+            if (((m >> lane) & 1ull) && rank < kBatch) sh.list[wave][rank] = lj;
+            fence();
+            // the batch as two tiles of 16 rows, in MFMA operand order
+            const int g = lane >> 4, c16 = lane & 15;
+            Blk<T, D> q[2];
+            int tmin = k, jo[2][4];
+#pragma unroll
+            for (int b2 = 0; b2 < 2; ++b2) {
+                const int jr = sh.list[wave][min(16 * b2 + c16, cnt - 1)];
+#pragma unroll
+                for (int v = 0; v < NV; ++v) q[b2].v[v] = load16(qh + (size_t)jr * D + (4 * v + g) * EV);
+                tmin = min(tmin, (int)seen[jr]);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) jo[b2][v] = sh.list[wave][min(16 * b2 + 4 * g + v, cnt - 1)];
+            }
+            tmin = (int)dev::wave_min_u32((unsigned)tmin);
+            unsigned low_key[2][4];  // inverted keys: the largest cosine is the smallest
+#pragma unroll
+            for (int b2 = 0; b2 < 2; ++b2)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) low_key[b2][v] = ~key[jo[b2][v]];
+            // picks 16 t + c16; the first pick's cosines all come from its pass
+            for (int t16 = tmin >> 4; 16 * t16 < k; ++t16) {
+                const int p = 16 * t16 + c16;
+                const bool valid = p >= 1 && p < k;
+                Blk<T, D> pk;
+#pragma unroll
+                for (int v = 0; v < NV; ++v) pk.v[v] = prow[min(p, k - 1) * LDP + 4 * v + g];
+                const float ip = inv[sh.pick[min(p, k - 1)]];
+#pragma unroll
+                for (int b2 = 0; b2 < 2; ++b2) {
+                    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+                    gram_mma<D>(acc, q[b2], pk);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        unsigned x = valid ? ~dev::ord_key(acc[v] * inv[jo[b2][v]] * ip) : ~0u;
+                        x = dev::dpp_min_u32<0xb1>(x);
+                        x = dev::dpp_min_u32<0x4e>(x);
+                        x = dev::dpp_min_u32<0x141>(x);
+                        x = dev::dpp_min_u32<0x140>(x);
+                        low_key[b2][v] = min(low_key[b2][v], x);
+                    }
+                }
+            }
+            // lane v of the 16 that hold rows 4 g .. 4 g + 3 stores row 4 g + v
+#pragma unroll
+            for (int b2 = 0; b2 < 2; ++b2)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (c16 == v && 16 * b2 + 4 * g + v < cnt) {
+                        const unsigned kk = ~low_key[b2][v];
+                        key[jo[b2][v]] = kk;
+                        seen[jo[b2][v]] = (unsigned char)k;
+                        atomicMin(low, ((unsigned long long)kk << 32) | (unsigned)jo[b2][v]);
+                    }
+            fence();
+        }
+        if (lane == 0) sh.post[wave] = mine;
+        __syncthreads();
+        unsigned long long gb = ~0ull;
+#pragma unroll
+        for (int w = 0; w < kLazyWaves; ++w) gb = min(gb, sh.post[w]);
+        // an unpicked row exists while k < min(m, n); the clamp only keeps
+        // the accesses below in bounds whatever the keys hold
+        const int r = min(max(__builtin_amdgcn_readfirstlane((int)(unsigned)gb), 0), n - 1);
+        if (wave == 0) {
+            if (lane < CPR) prow[k * LDP + lane] = load16(qh + (size_t)r * D + lane * EV);
+            if (lane == 0) {
+                sh.pick[k] = r;
+                if (picks) picks[(size_t)h * kmax + k] = r;
+                key[r] = kPicked;
+                *low = ~0ull;  // for the pick after the next
+            }
+        }
+        __syncthreads();
+        if (k == 0 && kmax > 1) {
+            float v[EV];
+            Elt<T>::unpack(prow[c], v);
+            project(false, v, inv[r], 1);
+        }
+    }
+
+    if (dst) {
+        // the picked rows are in LDS, so dst may be src
+        const size_t drow_bytes = (size_t)D * ((sizeof(T) == 2 && widen) ? 4 : sizeof(T));
+        char* dh = static_cast<char*>(dst) + (size_t)h * dst_rows * drow_bytes;
+        for (int i = t; i < kmax * CPR; i += kLazyThreads)
+            store_chunk<T, D>(dh + (size_t)(i / CPR) * drow_bytes, i % CPR, prow[i / CPR * LDP + i % CPR], widen);
+    }
+    write_counts(counts, h, dst_rows, kmax, t, kLazyThreads);
+}
+
 // ---- 64 < n <= 1024, bf16: rows resident in MFMA operand registers ------------
 
 constexpr int kRegThreads = 512;
@@ -689,6 +1024,23 @@ hipError_t launch_typed(int H, int n, int kmax, const void* src, int src_rows, i
         else if (nb <= 4) BKV_FPS_REG(4);
         else BKV_FPS_REG(kRegMaxNB);
 #undef BKV_FPS_REG
+        return hipGetLastError();
+    }
+    // Where the lazy kernel is ahead of re-reading every row for every pick
+    // (m = 16 unless stated): 8 to 512 heads of 1024 rows or more of 256 or
+    // 512 bytes (8 fp32 heads of 1024 x 64: 131 against 149 us; 8 bf16 heads
+    // of 1100 x 128: 117 against 198; 16384 rows: 983 against 2203).  Below
+    // 1024 fp32 rows a wave has too few rows per step (32 heads of 300 x 64:
+    // 99 against 58).  Rows of 128 bytes are cheap to re-read: 8 heads gain
+    // between 2048 and 8192 rows only (m = 8: 2000 rows 91 against 89, 3000
+    // 119 against 128, 5000 192 against 206, 16000 691 against 617), but
+    // with a head per compute unit the re-reads no longer come from L2 (512
+    // heads of 1500: 114 against 170).
+    const bool lazy = sizeof(T) * D == 128 ? H >= 256 || (n >= 2048 && n <= 8192) : true;
+    if (lazy && n >= 1024 && kmax <= kLazyMaxPicks && lazy_lds_bytes<T, D>(n, kmax) <= kLazyMaxLds) {
+        const size_t lds = lazy_lds_bytes<T, D>(n, kmax);
+        hipLaunchKernelGGL((fps_lazy_kernel<T, D>), dim3(H), dim3(kLazyThreads), lds, s, q, src_rows, n, kmax, picks, dst,
+                           widen, dst_rows, counts);
         return hipGetLastError();
     }
     const int rows_per_thread = (n + kStreamThreads - 1) / kStreamThreads;

@@ -155,6 +155,52 @@ def test_fps_large_sets(dtype, D, n, m, H):
     say(f"fps {dtype} D={D} n={n} m={m} H={H}: {ex}/{tot} picks exact before the first near tie")
 
 
+# The lazy kernel (rows brought up to date only where they can be the
+# argmin): its smallest sets, ragged ones, batches and pick tiles of 16 and
+# 32 crossed, one pick, the most picks it takes (128) and one more, 128-byte
+# rows with few and with many heads.
+LAZY_CASES = [("fp32", 64, 1024, 16, 3), ("fp32", 128, 1027, 34, 2), ("bf16", 128, 1025, 1, 2), ("bf16", 128, 1031, 2, 3),
+              ("bf16", 128, 1500, 128, 2), ("bf16", 128, 1500, 129, 1), ("bf16", 128, 4096, 17, 2),
+              ("bf16", 64, 2048, 33, 2), ("bf16", 64, 1030, 16, 256), ("fp32", 128, 3001, 16, 1)]
+
+
+@pytest.mark.parametrize("dtype,D,n,m,H", LAZY_CASES)
+def test_fps_lazy_sets(dtype, D, n, m, H):
+    q = queries(H, n, D, dtype, seed=n * 3 + m)
+    if n % 2:  # zero rows (cosine 0 with everything) and repeated rows (ties) among them
+        q[:, :, 5::97] = 0
+        q[:, :, 11::53] = q[:, :, 10:11]
+    before = host(q)
+    picks = torch.empty(1, H, m, dtype=torch.int32, device="cuda")
+    dst = torch.full((1, H, m + 3, D), 7.0, dtype=torch.float32, device="cuda")
+    if m <= 128:
+        bkv.fps_gather(q, m, dst=dst, picks=picks)
+        p = host(picks)
+        rows = torch.gather(before.float(), 2, p.long().unsqueeze(-1).expand(-1, -1, -1, D))
+        assert torch.equal(host(dst)[:, :, :m], rows) and (host(dst)[:, :, m:] == 7.0).all()
+        bkv.fps_gather(q, m)  # in place: the same selection
+        assert torch.equal(host(q)[:, :, :m].float(), rows) and torch.equal(host(q)[:, :, m:], before[:, :, m:])
+    else:
+        p = host(bkv.fps(q, m))
+    some = slice(0, min(H, 3))
+    check_against_oracle(before[:, some].contiguous(), p[:, some].contiguous(), m)
+
+
+def test_fps_lazy_repeated_axes():
+    # every average is 0 and every S ties (see the closed form above), so
+    # every pick is settled by the index alone, across the waves' row runs
+    q, _ = _golden("tie_query", 128)
+    x = torch.from_numpy(np.tile(q[0], (400, 1))[None]).to(torch.bfloat16).cuda()
+    assert host(bkv.fps(x, 40))[0].tolist() == [0, 2, 1, 3] + list(range(4, 40))
+
+
+def test_fps_lazy_largest_set_greedy_rule():
+    q = queries(2, 16384, 128, "bf16", seed=16384)
+    picks = bkv.fps(q, 16)
+    torch.cuda.synchronize()
+    check_greedy_rule(host(q), host(picks), 16)
+
+
 @pytest.mark.parametrize("n", [20000, 32768])
 def test_fps_largest_sets_greedy_rule(n):
     q = queries(2, n, 128, "bf16", seed=n)
