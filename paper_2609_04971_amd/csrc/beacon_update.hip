@@ -61,6 +61,56 @@ __device__ __forceinline__ float row_dot(const float* a, const float* b) {
 // loads in flight (a workgroup-scope fence or barrier would).
 __device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront"); }
 
+__device__ __forceinline__ float cosine(float dot, float xn, float bn) {
+    return (xn == 0.f || bn == 0.f) ? 0.f : dot * __builtin_amdgcn_rsqf(xn) * __builtin_amdgcn_rsqf(bn);
+}
+
+// The slot of largest cosine with the query xs (squared norm xn), ties ->
+// lowest slot: the smallest inverted order key of the cosine over the wave,
+// then the lowest lane that holds it.  The cosine takes hardware reciprocal
+// square roots (about 1 ulp each), so the choice can differ from exact
+// arithmetic only where the two best cosines lie within a few 1e-7 of each
+// other.  bl [C][D + 4], xs [D] and the slots' squared norms bn2 in LDS.
+// QUAD (C <= 16): lanes 4c .. 4c+3 each take a quarter of slot c; else lane
+// c takes slot c.
+template <int D, bool QUAD>
+__device__ __forceinline__ int nearest_slot(const float* bl, const float* xs, const float* bn2, float xn, int C,
+                                            int lane) {
+    constexpr int LD = D + 4, QD = D / 4;
+    unsigned key = ~0u;
+    bool holds;  // this lane speaks for a slot
+    if constexpr (QUAD) {
+        const int c = lane >> 2, part = lane & 3;
+        const float dot = dev::quad_sum(c < C ? row_dot<QD>(&bl[c * LD + part * QD], &xs[part * QD]) : 0.f);
+        holds = c < C && part == 0;
+        if (holds) key = ~dev::ord_key(cosine(dot, xn, bn2[c]));
+    } else {
+        const float dot = (lane < C) ? row_dot<D>(&bl[lane * LD], xs) : 0.f;
+        holds = lane < C;
+        if (holds) key = ~dev::ord_key(cosine(dot, xn, bn2[lane]));
+    }
+    const unsigned kmin = dev::wave_min_u32(key);
+    return (__ffsll(__ballot(holds && key == kmin)) - 1) >> (QUAD ? 2 : 0);
+}
+
+// Squared norm of a quarter of a row, summed over its four lanes.
+template <int D>
+__device__ __forceinline__ float quarter_norm(const float* quarter, bool live) {
+    float p = 0.f;
+    if (live) {
+        const float4* r = reinterpret_cast<const float4*>(quarter);
+#pragma unroll
+        for (int d4 = 0; d4 < D / 16; ++d4) {
+            const float4 u = r[d4];
+            p = fmaf(u.x, u.x, p);
+            p = fmaf(u.y, u.y, p);
+            p = fmaf(u.z, u.z, p);
+            p = fmaf(u.w, u.w, p);
+        }
+    }
+    return dev::quad_sum(p);
+}
+
 constexpr int kMaxSlots = 64;   // the boundary rejects C > 64: one bit per slot in a 64-bit mask
 constexpr int kLoadChunk = 8;   // 16-byte beacon loads in flight per thread
 constexpr int kQuadSlots = 16;  // C up to this: one wave per head, four lanes per slot's dot product
@@ -137,19 +187,7 @@ __global__ __launch_bounds__(64 * NW) void beacon_update_kernel(const T* __restr
     // squared norms: four threads per slot
     for (int c0 = 0; c0 < C; c0 += NT / 4) {
         const int c = c0 + (tid >> 2), part = tid & 3;
-        float p = 0.f;
-        if (c < C) {
-            const float4* r = reinterpret_cast<const float4*>(&bl[c * LD + part * QD]);
-#pragma unroll
-            for (int d4 = 0; d4 < QD / 4; ++d4) {
-                const float4 u = r[d4];
-                p = fmaf(u.x, u.x, p);
-                p = fmaf(u.y, u.y, p);
-                p = fmaf(u.z, u.z, p);
-                p = fmaf(u.w, u.w, p);
-            }
-        }
-        p = dev::quad_sum(p);
+        const float p = quarter_norm<D>(&bl[c * LD + part * QD], c < C);
         if (c < C && part == 0) bn2[c] = p;
     }
     sync();
@@ -182,35 +220,7 @@ __global__ __launch_bounds__(64 * NW) void beacon_update_kernel(const T* __restr
                     bn2[chosen] = xn;
                 }
             } else {
-                // argmax over the slots, ties -> lowest slot: the smallest
-                // inverted order key of the cosine over the wave, then the
-                // lowest lane that holds it.  The cosine takes hardware
-                // reciprocal square roots (about 1 ulp each), so the choice can
-                // differ from exact arithmetic only where the two best cosines
-                // lie within a few 1e-7 of each other.
-                const float rx = __builtin_amdgcn_rsqf(xn);
-                auto cosine = [&](float dot, float bn) {
-                    return (xn == 0.f || bn == 0.f) ? 0.f : dot * rx * __builtin_amdgcn_rsqf(bn);
-                };
-                unsigned key = ~0u;
-                bool holds;  // this lane speaks for a slot
-                int shift;   // lane -> slot
-                if constexpr (NW == 1) {
-                    // C <= 16: lanes 4c .. 4c+3 each take a quarter of slot c
-                    const int c = lane >> 2, part = lane & 3;
-                    const float dot = dev::quad_sum(c < C ? row_dot<QD>(&bl[c * LD + part * QD], &xs[part * QD]) : 0.f);
-                    holds = c < C && part == 0;
-                    if (holds) key = ~dev::ord_key(cosine(dot, bn2[c]));
-                    shift = 2;
-                } else {
-                    // lane c takes slot c
-                    const float dot = (lane < C) ? row_dot<D>(&bl[lane * LD], xs) : 0.f;
-                    holds = lane < C;
-                    if (holds) key = ~dev::ord_key(cosine(dot, bn2[lane]));
-                    shift = 0;
-                }
-                const unsigned kmin = dev::wave_min_u32(key);
-                chosen = (__ffsll(__ballot(holds && key == kmin)) - 1) >> shift;
+                chosen = nearest_slot<D, NW == 1>(bl, xs, bn2, xn, C, lane);
                 const int n = cnt[chosen] + 1;
                 const float inv = 1.0f / (float)n;
                 float p = 0.f;
@@ -244,6 +254,373 @@ __global__ __launch_bounds__(64 * NW) void beacon_update_kernel(const T* __restr
     if (tid < C && ((dirty >> tid) & 1ull)) counts[(size_t)h * C + tid] = cnt[tid];
 }
 
+// ---- many queries per head ---------------------------------------------------
+//
+// A prompt's queries are one chain per head, and the kernel above spends
+// 0.5 to 1.3 us on each: a dot product with every slot, an argmax and the
+// update of a row, all dependent.  Here 16 queries are taken at a time.  Their
+// dot products with every slot (the beacons stay in registers) and with each other come
+// from MFMA, and the chain then works on those numbers only: one wave, lane
+// = slot, picks the slot and applies the update to the slot's remaining dot
+// products and its squared norm,
+//     <x', b + (x - b)/n> = <x', b> + (<x', x> - <x', b>)/n,
+//     |b + (x - b)/n|^2 = (1 - 1/n)^2 |b|^2 + |x|^2/n^2 + 2 (1 - 1/n)/n <x, b>,
+// after which the waves apply the batch's updates to the beacons themselves,
+// query by query with the same arithmetic as above, and take the norms
+// afresh.  The numbers of a batch carry a few more roundings than direct
+// ones (a few 1e-7 of a cosine).  So a query whose two best cosines lie
+// within kNearTie is settled from the beacons themselves with the arithmetic
+// above (about one in 10^4), and where an update cancels most of a beacon
+// the batch ends, so that the next one starts from the beacons again: the
+// choices are those of the kernel above, and so are the results.
+//
+// Bound by the chain, about 100 instructions a query on one wave, and by the
+// batch's phases around it.  128 heads of 2048 queries: 64 slots 942 us
+// (2590 with the kernel above), 16 slots 990 (1761); 4608 heads of 256
+// queries, 64 slots: 860 (1850).
+constexpr int kBatchQ = 16;   // queries per batch: one MFMA tile
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+
+template <int D, int NW>
+struct alignas(16) BatchLds {
+    static constexpr int QP = D / 4 + 4;  // a quarter of a query, padded
+    float xs[2][kBatchQ][4 * QP];         // this batch's queries and the next one's
+    float dot[kBatchQ][16 * NW + 4];      // <query, slot>
+    float gram[kBatchQ][kBatchQ + 4];     // <query, query>
+    float margin[kBatchQ];                // near-tie margin of each query's products
+    float bn2[16 * NW];                   // squared norm of each slot
+    struct {
+        int slot;   // the slot a query joined; + kFill: it filled an empty one
+        float inv;  // 1/n of the update
+    } joined[kBatchQ];
+    float row[D], x0[D];                  // a beacon and the query of a choice settled directly
+    unsigned long long near;              // the slots it is between
+    int done;                             // queries of the batch that were taken; 0: settle the first directly
+    unsigned long long dirty;
+};
+constexpr int kFill = 256;
+constexpr float kNearTie = 4e-6f;  // cosines this close are settled by the arithmetic of one query at a time
+constexpr int kBatchMin = 16;  // queries per head from which the batches are taken
+
+// Maximum over the wave, the same in every lane.
+template <int CTRL>
+__device__ __forceinline__ int dpp_max_i32(int v) {
+    const int w = __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false);
+    return w > v ? w : v;
+}
+__device__ __forceinline__ int wave_max_i32(int v) {
+    v = dpp_max_i32<0x140>(dpp_max_i32<0x141>(dpp_max_i32<0x4e>(dpp_max_i32<0xb1>(v))));
+    return max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+               max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+}
+
+// NW = ceil(C / 16) waves; wave w holds slots 16 w .. 16 w + 15, lane (g =
+// lane / 16, c = lane % 16) elements g D/4 .. (g + 1) D/4 - 1 of slot 16 w + c.
+template <typename T, int D, int NW>
+__global__ __launch_bounds__(64 * NW) void beacon_batch_kernel(const T* __restrict__ q_new, int T_steps, float* beacons,
+                                                              int32_t* counts, int32_t* assign, int Hq, int Hkv, int C) {
+    constexpr int NT = 64 * NW, Q = D / 4, EV = 16 / (int)sizeof(T), CPR = D / EV;  // 16-byte chunks per query
+    constexpr int NL = (kBatchQ * CPR + NT - 1) / NT;                                // chunks per thread of a batch
+    using L = BatchLds<D, NW>;
+    __shared__ L sh;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, c16 = lane & 15;
+    const int h = blockIdx.x, b = h / Hkv, kh = h % Hkv, G = Hq / Hkv;
+    const int nq = T_steps * G;
+    float* bh = beacons + (size_t)h * C * D;
+    const int slot = wave * 16 + c16;
+
+    dev::u32x4 xr[NL];
+    auto load_queries = [&](int base) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const int id = tid + NT * i, qq = base + id / CPR;
+            xr[i] = dev::u32x4{0u, 0u, 0u, 0u};
+            if (id < kBatchQ * CPR && qq < nq) {
+                const int t = qq / G, gq = qq - t * G;
+                xr[i] = *reinterpret_cast<const dev::u32x4*>(
+                    q_new + (((size_t)b * Hq + (size_t)kh * G + gq) * T_steps + t) * D + id % CPR * EV);
+            }
+        }
+    };
+    auto stage_queries = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const int id = tid + NT * i;
+            if (id < kBatchQ * CPR) {
+                const int e0 = id % CPR * EV;  // EV divides a quarter
+                float* o = &sh.xs[buf][id / CPR][e0 / Q * L::QP + e0 % Q];
+#pragma unroll
+                for (int w = 0; w < EV; w += 4) {
+                    f32x4 v;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        if constexpr (sizeof(T) == 2) {
+                            const unsigned u = xr[i][(w + e) / 2];
+                            v[e] = __uint_as_float(e & 1 ? u & 0xffff0000u : u << 16);
+                        } else {
+                            v[e] = __uint_as_float(xr[i][e]);
+                        }
+                    }
+                    *reinterpret_cast<f32x4*>(o + w) = v;
+                }
+            }
+        }
+    };
+    load_queries(0);
+    f32x4 beta[Q / 4];
+#pragma unroll
+    for (int i = 0; i < Q / 4; ++i)
+        beta[i] = slot < C ? reinterpret_cast<const f32x4*>(bh + (size_t)slot * D + g * Q)[i] : f32x4{0.f, 0.f, 0.f, 0.f};
+    int cnt = (wave == 0 && lane < C) ? counts[(size_t)h * C + lane] : 1;  // wave 0: lane = slot
+    bool touched = false;          // wave 0: this lane's slot changed
+    unsigned long long dirty = 0;  // wave 0: the slots that did
+    auto store_norms = [&] {
+        float p = 0.f;
+#pragma unroll
+        for (int i = 0; i < Q / 4; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p = fmaf(beta[i][e], beta[i][e], p);
+        p += dev::shfl_xor_f(p, 16);
+        p += dev::shfl_xor_f(p, 32);
+        if (g == 0) sh.bn2[slot] = p;
+    };
+    store_norms();
+    stage_queries(0);
+    __syncthreads();
+
+    int buf = 0;
+    for (int base = 0; base < nq;) {
+        load_queries(base + kBatchQ);  // the next batch, unless this one ends early
+        // dot products with the wave's slots; wave 0: with each other too
+        {
+            f32x4 x[Q / 4];
+#pragma unroll
+            for (int i = 0; i < Q / 4; ++i) x[i] = *reinterpret_cast<const f32x4*>(&sh.xs[buf][c16][g * L::QP + 4 * i]);
+            f32x4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = a0;
+#pragma unroll
+            for (int i = 0; i < Q / 4; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; e += 2) {
+                    a0 = __builtin_amdgcn_mfma_f32_16x16x4f32(beta[i][e], x[i][e], a0, 0, 0, 0);
+                    a1 = __builtin_amdgcn_mfma_f32_16x16x4f32(beta[i][e + 1], x[i][e + 1], a1, 0, 0, 0);
+                }
+            // rows 4 g + v: slots, column c16: the query
+            *reinterpret_cast<f32x4*>(&sh.dot[c16][wave * 16 + 4 * g]) = a0 + a1;
+            if (wave == 0) {
+                f32x4 r = {0.f, 0.f, 0.f, 0.f};
+                if constexpr (sizeof(T) == 2) {  // the queries are bf16 values: exact in bf16
+#pragma unroll
+                    for (int i = 0; i < Q / 4; i += 2) {
+                        dev::u32x4 o;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const f32x4& y = x[i + (e >> 1)];
+                            o[e] = (__float_as_uint(y[2 * (e & 1)]) >> 16) | __float_as_uint(y[2 * (e & 1) + 1]);
+                        }
+                        const bf16x8_t f = __builtin_bit_cast(bf16x8_t, o);
+                        r = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, f, r, 0, 0, 0);
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < Q / 4; ++i)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) r = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i][e], x[i][e], r, 0, 0, 0);
+                }
+                *reinterpret_cast<f32x4*>(&sh.gram[c16][4 * g]) = r;  // symmetric
+            }
+        }
+        __syncthreads();
+        if (wave == 0) {  // the chain
+            int done = min(kBatchQ, nq - base);
+            const unsigned long long empty = __ballot(lane < C && cnt == 0);
+            if (empty) {
+                // while slots are empty each query fills the lowest one; the
+                // batch ends with the last
+                done = min(done, (int)__popcll(empty));
+                const int q = __popcll(empty & ((1ull << lane) - 1));
+                if (((empty >> lane) & 1ull) && q < done) {
+                    cnt = 1;
+                    sh.joined[q] = {lane | kFill, 0.f};
+                    touched = true;
+                }
+            } else {
+                // lanes past C never hold the largest product
+                const int ls = min(lane, C - 1);
+                const bool mine = lane < C;
+                float d[kBatchQ];
+#pragma unroll
+                for (int q = 0; q < kBatchQ; ++q) d[q] = mine ? sh.dot[q][ls] : -INFINITY;
+                float bn = mine ? sh.bn2[ls] : 1.f;
+                // 1/|b| (0 for a zero beacon), 1/n of the slot's next update
+                auto inv_root = [](float x) { return x == 0.f ? 0.f : __builtin_amdgcn_rsqf(x); };
+                auto inv_count = [](int n) {  // one Newton step past the 1-ulp reciprocal
+                    const float f = (float)n, r = __builtin_amdgcn_rcpf(f);
+                    return fmaf(fmaf(-f, r, 1.f), r, r);
+                };
+                float rb = inv_root(bn), inv = inv_count(cnt + 1);
+                // the near-tie margin of each query, beside its products
+                if (lane < kBatchQ) sh.margin[lane] = kNearTie * sqrtf(sh.gram[lane][lane]);
+                wave_lds_fence();
+                f32x4 gr[2][4];  // <query q, the others> and its margin, read one query ahead
+                float margin[2];
+                auto fetch = [&](auto q) {
+#pragma unroll
+                    for (int o = q / 4; o < 4; ++o) gr[q & 1][o] = *reinterpret_cast<const f32x4*>(&sh.gram[q][4 * o]);
+                    margin[q & 1] = sh.margin[q];
+                };
+                fetch(std::integral_constant<int, 0>{});
+                dev::static_for<kBatchQ>([&](auto q) {
+                    if constexpr (q + 1 < kBatchQ) fetch(std::integral_constant<int, q + 1>{});
+                    if (q >= done) return;  // uniform
+                    const f32x4* gq = gr[q & 1];
+                    const float xn = gq[q / 4][q % 4];
+                    // the cosines but for the common factor 1/|x|, which moves
+                    // no argmax (a zero query has all its products 0), as
+                    // integers of the same order (-0 as +0)
+                    int key = __float_as_int(fmaf(d[q], rb, 0.f));
+                    key ^= (key >> 31) & 0x7fffffff;
+                    const int top = wave_max_i32(key);
+                    const unsigned long long at = __ballot(key == top);
+                    const int chosen = __ffsll(at) - 1;
+                    // another cosine within rounding of the largest: end the
+                    // batch before this query, or settle it if it is the first
+                    // (equal products of equal norms: the lowest, as ever)
+                    const int tb = top ^ ((top >> 31) & 0x7fffffff);
+                    const unsigned long long near = __ballot(d[q] * rb >= __int_as_float(tb) - margin[q & 1]);
+                    if (near & (near - 1)) {
+                        const float nb = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bn), chosen));
+                        if (xn != 0.f && near != __ballot(key == top && bn == nb)) {
+                            done = q;
+                            if (q == 0 && lane == 0) sh.near = near;
+                            return;
+                        }
+                    }
+                    const float keep = 1.f - inv;
+                    const float parts = fmaf(keep * keep, bn, inv * inv * xn);
+                    const float nbn = fmaf(2.f * inv * keep, d[q], parts);
+                    // most of the beacon cancels: start over from the updated beacons
+                    const unsigned long long cancels = __ballot(!(nbn >= 0.25f * parts));
+                    if ((cancels >> chosen) & 1ull) done = q + 1;
+                    if (lane == chosen) {
+                        sh.joined[q] = {lane, inv};
+                        touched = true;
+                        ++cnt;
+                        bn = nbn;
+#pragma unroll
+                        for (int o = q + 1; o < kBatchQ; ++o) d[o] = fmaf(gq[o / 4][o % 4] - d[o], inv, d[o]);
+                    }
+                    rb = inv_root(bn);
+                    inv = inv_count(cnt + 1);
+                });
+            }
+            dirty = __ballot(touched);
+            if (lane >= done && lane < kBatchQ) sh.joined[lane] = {-1, 0.f};
+            if (lane == 0) {
+                sh.done = done;
+                sh.dirty = dirty;
+            }
+        }
+        __syncthreads();
+        int done = __builtin_amdgcn_readfirstlane(sh.done);
+        if (done == 0) {
+            // the first query's choice is within rounding: it is settled
+            // between the slots that are, one after the other, as
+            // beacon_update_kernel forms their cosines, bit for bit, norms
+            // included (a changed slot's is summed over the wave, another's
+            // over four lanes)
+            for (int i = tid; i < D; i += NT) sh.x0[i] = sh.xs[buf][0][i / Q * L::QP + i % Q];
+            int chosen = 0;
+            unsigned best = ~0u;
+            for (unsigned long long m = sh.near; m; m &= m - 1) {
+                const int c = __ffsll(m) - 1;
+                if (slot == c) {
+#pragma unroll
+                    for (int i = 0; i < Q / 4; ++i) *reinterpret_cast<f32x4*>(&sh.row[g * Q + 4 * i]) = beta[i];
+                }
+                __syncthreads();
+                if (wave == 0) {
+                    auto sumsq = [&](const float* r) {
+                        float p = 0.f;
+#pragma unroll
+                        for (int k = 0; k < D / 64; ++k) p = fmaf(r[lane + 64 * k], r[lane + 64 * k], p);
+                        return dev::wave_sum(p);
+                    };
+                    const int part = (lane & 3) * Q;
+                    const float bn = ((dirty >> c) & 1ull) ? sumsq(sh.row) : quarter_norm<D>(&sh.row[part], true);
+                    const float dot = NW == 1 ? dev::quad_sum(row_dot<Q>(&sh.row[part], &sh.x0[part]))
+                                              : row_dot<D>(sh.row, sh.x0);
+                    const unsigned key = __builtin_amdgcn_readfirstlane(~dev::ord_key(cosine(dot, sumsq(sh.x0), bn)));
+                    if (key < best) {
+                        best = key;
+                        chosen = c;
+                    }
+                }
+                __syncthreads();
+            }
+            if (wave == 0) {
+                if (lane == chosen) {
+                    touched = true;
+                    ++cnt;
+                    sh.joined[0] = {lane, 1.0f / (float)cnt};
+                }
+                dirty = __ballot(touched);
+                if (lane == 0) sh.dirty = dirty;
+            }
+            __syncthreads();
+            done = 1;
+        }
+        if (assign && tid < done) assign[(size_t)h * nq + base + tid] = sh.joined[tid].slot & (kFill - 1);
+        // the batch's updates, every slot's in order (its queries all fill, or
+        // all join)
+        const bool fills = __builtin_amdgcn_readfirstlane(sh.joined[0].slot & kFill) != 0;
+        unsigned todo = 0;
+#pragma unroll
+        for (int q = 0; q < kBatchQ; ++q) {
+            const int at = sh.joined[q].slot;  // -1: not taken
+            todo |= (at == slot || at == (slot | kFill)) ? 1u << q : 0u;
+        }
+        while (__ballot(todo != 0)) {
+            if (todo) {
+                const int q = __ffs(todo) - 1;
+                todo &= todo - 1;
+                const float inv = sh.joined[q].inv;
+#pragma unroll
+                for (int i = 0; i < Q / 4; ++i) {
+                    const f32x4 x = *reinterpret_cast<const f32x4*>(&sh.xs[buf][q][g * L::QP + 4 * i]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) beta[i][e] = fills ? x[e] : beta[i][e] + (x[e] - beta[i][e]) * inv;
+                }
+            }
+        }
+        store_norms();
+        base += done;
+        if (done < kBatchQ && base < nq) load_queries(base);
+        stage_queries(buf ^ 1);
+        buf ^= 1;
+        __syncthreads();
+    }
+    const unsigned long long changed = sh.dirty;
+    if (slot < C && ((changed >> slot) & 1ull)) {
+#pragma unroll
+        for (int i = 0; i < Q / 4; ++i) reinterpret_cast<f32x4*>(bh + (size_t)slot * D + g * Q)[i] = beta[i];
+    }
+    if (wave == 0 && lane < C && ((changed >> lane) & 1ull)) counts[(size_t)h * C + lane] = cnt;
+}
+
+template <typename T, int D>
+void launch_batch(const bkv_dims& d, const T* q_new, int T_steps, float* beacons, int32_t* counts, int32_t* assign,
+                  hipStream_t s) {
+    const dim3 grid(d.B * d.Hkv);
+    switch ((d.C + 15) / 16) {
+        case 1: hipLaunchKernelGGL((beacon_batch_kernel<T, D, 1>), grid, dim3(64), 0, s, q_new, T_steps, beacons, counts, assign, d.Hq, d.Hkv, d.C); break;
+        case 2: hipLaunchKernelGGL((beacon_batch_kernel<T, D, 2>), grid, dim3(128), 0, s, q_new, T_steps, beacons, counts, assign, d.Hq, d.Hkv, d.C); break;
+        case 3: hipLaunchKernelGGL((beacon_batch_kernel<T, D, 3>), grid, dim3(192), 0, s, q_new, T_steps, beacons, counts, assign, d.Hq, d.Hkv, d.C); break;
+        default: hipLaunchKernelGGL((beacon_batch_kernel<T, D, 4>), grid, dim3(256), 0, s, q_new, T_steps, beacons, counts, assign, d.Hq, d.Hkv, d.C); break;
+    }
+}
+
 }  // namespace
 
 hipError_t launch_beacon_update(const bkv_dims& d, const void* q_new, int T, float* beacons, int32_t* counts,
@@ -251,6 +628,21 @@ hipError_t launch_beacon_update(const bkv_dims& d, const void* q_new, int T, flo
     const int P = d.B * d.Hkv;
     if (P == 0 || T == 0) return hipSuccess;
     const bool bf = d.dtype == BKV_BF16;
+    // 16 queries or more per head (a batch), readable 16 bytes at a time: from
+    // there on the batches are ahead on every shape measured (16 queries:
+    // 8 heads of 16 slots 11 us against 17, 4608 heads of 16 slots 41 against
+    // 48, of 64 slots 76 against 135)
+    if ((long long)T * (d.Hq / d.Hkv) >= kBatchMin && (reinterpret_cast<uintptr_t>(q_new) & 15) == 0) {
+        if (bf && d.D == 128)
+            launch_batch<uint16_t, 128>(d, static_cast<const uint16_t*>(q_new), T, beacons, counts, assign, s);
+        else if (bf)
+            launch_batch<uint16_t, 64>(d, static_cast<const uint16_t*>(q_new), T, beacons, counts, assign, s);
+        else if (d.D == 128)
+            launch_batch<float, 128>(d, static_cast<const float*>(q_new), T, beacons, counts, assign, s);
+        else
+            launch_batch<float, 64>(d, static_cast<const float*>(q_new), T, beacons, counts, assign, s);
+        return hipGetLastError();
+    }
 #define BKV_LAUNCH_BU(TY, DD)                                                                                   \
     if (d.C <= kQuadSlots)                                                                                  \
         hipLaunchKernelGGL((beacon_update_kernel<TY, DD, 1>), dim3(P), dim3(64), smem_bytes<DD>(d.C), s,            \

@@ -145,3 +145,62 @@ def test_beacon_update_long_stream_stepwise_resync():
             say(f"  step {t + 1}: {compared} head-steps compared, worst rel err {worst:.2e}, "
                 f"{ties} near ties flagged, {tie_diffs} resolved differently")
     assert int(gc.sum()) == int(x["counts"].sum()) + steps * d.B * d.Hq  # counts sum to queries seen
+
+
+# ---- 16 queries or more per head: taken in batches of 16 ---------------------------
+BATCH_CASES = [  # dtype, D, Hkv, G, T, C: batches of 16 crossed by 0 and 1, 1 to 4 slot tiles and their edges
+    ("bf16", 128, 3, 4, 4, 16), ("bf16", 128, 2, 1, 17, 17), ("fp32", 64, 2, 7, 5, 64), ("bf16", 64, 2, 2, 24, 1),
+    ("fp32", 128, 2, 4, 8, 33), ("bf16", 128, 2, 4, 12, 48)]
+
+
+def _batch_inputs(dtype, D, Hkv, G, T, C, seed):
+    w = synth.Workload("b", B=2, Hq=Hkv * G, Hkv=Hkv, D=D, N=1, W=0, C=C, budget=1, dtype=dtype)
+    x = synth.make_layer(w, seed=seed, N_cap=1)
+    d = bkv.dims(B=2, Hq=Hkv * G, Hkv=Hkv, D=D, N=1, W=0, C=C, budget=1, dtype=dtype)
+    return d, synth.query_stream(w, T, seed=seed), x["beacons"], x["counts"]
+
+
+@pytest.mark.parametrize("empty", [0, 1])
+@pytest.mark.parametrize("dtype,D,Hkv,G,T,C", BATCH_CASES)
+def test_batches_match_the_oracle(dtype, D, Hkv, G, T, C, empty):
+    d, q, b, c = _batch_inputs(dtype, D, Hkv, G, T, C, seed=C + T)
+    if empty:  # every other slot is filled first; with many slots, over more than one batch
+        c[..., ::2] = 0
+    say(f"beacon batches {dtype} D={D} G={G} T={T} C={C}: rel err {_check(d, q, b, c):.2g}")
+
+
+def test_batches_ties_zeros_and_cancellation():
+    # repeated beacons (the lowest of them wins), queries that cancel the
+    # beacon they join, zero queries and repeated queries: the choices of one
+    # step per call
+    d, q, b, c = _batch_inputs("bf16", 128, 2, 4, 16, 24, seed=3)
+    b[..., 12:, :] = b[..., :12, :]
+    b[..., 5, :] = 0
+    c[:] = 1
+    q[:, :, 3] = 0
+    q[:, :, 9] = q[:, :, 8]
+    q[:, :4, 6] = -b[:, 0, None, 2].to(q.dtype)
+    q[:, :4, 7] = b[:, 0, None, 2].to(q.dtype)
+    got = _run_gpu(d, q, b, c)
+    bs, cs, steps = b, c, []
+    for t in range(q.shape[2]):
+        bn, cn, a = _run_gpu(d, q[:, :, t:t + 1].contiguous(), bs, cs)
+        bs, cs = torch.from_numpy(bn), torch.from_numpy(cn)
+        steps.append(a)
+    np.testing.assert_array_equal(got[2], np.concatenate(steps, axis=-1))
+    np.testing.assert_array_equal(got[1], cn)
+    np.testing.assert_array_equal(got[0], bn)
+
+
+def test_many_queries_at_an_unaligned_address():
+    # not readable 16 bytes at a time: one query at a time, the same result
+    d, q, b, c = _batch_inputs("bf16", 64, 2, 4, 8, 16, seed=9)
+    raw = torch.empty(q.numel() + 1, dtype=q.dtype, device="cuda")
+    odd = raw[1:].view(q.shape)
+    odd.copy_(q)
+    assert odd.data_ptr() % 16
+    b2, c2 = b.cuda(), c.cuda()
+    bkv.beacon_update(d, odd, b2, c2)
+    ref = _run_gpu(d, q, b, c)
+    np.testing.assert_array_equal(host(b2).numpy(), ref[0])
+    np.testing.assert_array_equal(host(c2).numpy(), ref[1])
