@@ -289,6 +289,25 @@ bkv_status bkv_evict_noalloc(const bkv_dims* d, int32_t flags, void* K, void* V,
                              const float* rope_sin, float scale, int32_t* kept, float* scores, float* row_lse,
                              int32_t* device_status, hipStream_t stream);
 
+/* ---- Appending a decode step's rows ---------------------------------------------
+ * One launch that copies one row per head into each of n arrays (a step's
+ * keys and values into the cache, its queries into their buffers): for array
+ * i and head h < heads, row_bytes bytes from src + h * src_stride to
+ * dst + h * dst_stride (strides in bytes; dst already points at the row to
+ * write).  The rows written must not overlap one another or the sources.
+ * row_bytes is a positive multiple of 16; pointers and strides are multiples
+ * of 16; 0 <= n <= BKV_APPEND_MAX; heads >= 0 (0 writes nothing), at most
+ * 2^31 - 1 chunks of 16 bytes in all.  n == 0 enqueues nothing. */
+#define BKV_APPEND_MAX 4
+typedef struct {
+    const void* src;
+    void* dst;
+    int64_t src_stride;
+    int64_t dst_stride;
+    int64_t heads;
+} bkv_rows;
+bkv_status bkv_append_rows(const bkv_rows* arrays, int32_t n, int32_t row_bytes, hipStream_t stream);
+
 /* Static description of a status code. */
 const char* bkv_status_string(bkv_status s);
 

@@ -25,7 +25,8 @@ OP_BEACON_UPDATE, OP_SCORE, OP_TOPK, OP_COMPACT, OP_EVICT = range(5)
 EXPORTS = ("bkv_validate", "bkv_workspace_bytes", "bkv_workspace_init", "bkv_device_status",
            "bkv_beacon_update", "bkv_score", "bkv_topk", "bkv_compact", "bkv_evict",
            "bkv_score_ex", "bkv_evict_ex", "bkv_fps", "bkv_fps_gather", "bkv_status_string",
-           "bkv_abi_version", "bkv_compact_fill", "bkv_evict_noalloc")
+           "bkv_abi_version", "bkv_compact_fill", "bkv_evict_noalloc", "bkv_append_rows")
+APPEND_MAX = 4
 SCORE_MEAN, SCORE_CAUSAL = 1, 2
 
 
@@ -53,6 +54,15 @@ class Dims(ctypes.Structure):
 
     def __repr__(self):
         return "Dims(" + ", ".join(f"{n}={getattr(self, n)}" for n, _ in self._fields_) + ")"
+
+
+class Rows(ctypes.Structure):
+    """One array of append_rows: see bkv_rows."""
+    _fields_ = [("src", ctypes.c_void_p), ("dst", ctypes.c_void_p), ("src_stride", ctypes.c_int64),
+                ("dst_stride", ctypes.c_int64), ("heads", ctypes.c_int64)]
+
+
+_APPEND = [Rows * n for n in range(APPEND_MAX + 1)]
 
 
 def dims(B, Hq, Hkv, D, N, W, C, budget, n_prefix=0, dtype="bf16", N_cap=None) -> Dims:
@@ -83,6 +93,7 @@ _SIGS = {
     "bkv_evict_noalloc": ([_D, _I, _P, _P, _P, _P, _P, _P, _P, ctypes.c_float, _P, _P, _P, _P, _P], ctypes.c_int),
     "bkv_fps": ([_I] * 5 + [_P, _I, _P, _P], ctypes.c_int),
     "bkv_fps_gather": ([_I] * 5 + [_P, _I, _P, _I, _I, _P, _P, _P], ctypes.c_int),
+    "bkv_append_rows": ([ctypes.POINTER(Rows), _I, _I, _P], ctypes.c_int),
     "bkv_status_string": ([ctypes.c_int], ctypes.c_char_p),
     "bkv_abi_version": ([], ctypes.c_int32),
 }
@@ -133,7 +144,9 @@ def workspace_bytes(d: Dims, op: int = OP_EVICT) -> int:
 
 # ---- marshalling helpers ---------------------------------------------------
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current stream of the current device, as a plain handle (what
+    torch.cuda.current_stream().cuda_stream is, without a Stream object)."""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _tdtype(d: Dims):
@@ -287,6 +300,41 @@ def evict_noalloc(d: Dims, K, V, q_win, beacons, counts, kept=None, scores=None,
         _ptr(row_lse, (d.B, d.Hkv, d.C + d.G * d.W), torch.float32, "row_lse", optional=True),
         _ptr(status, (1,), torch.int32, "status", optional=True), _stream())
     _check(st, "bkv_evict_noalloc")
+
+
+# ---- appending a step's rows -------------------------------------------------------
+def append_rows(writes):
+    """dst[:, :, row] = src for every (dst [B, H, rows, D], row, src [B, H, D])
+    of `writes`, as one launch where bkv_append_rows can read and write them
+    (plain tensors of one dtype on one GPU, whole rows of 16-byte chunks, one
+    stride from head to head), else array by array."""
+    n = len(writes)
+    if 0 < n <= APPEND_MAX:
+        arrays = _APPEND[n]()
+        d0 = writes[0][0]
+        dtype, dev, D = d0.dtype, d0.get_device(), d0.shape[-1]
+        row_bytes = D * d0.element_size()
+        if dev >= 0 and dev == torch.cuda.current_device() and row_bytes % 16 == 0:
+            for a, (dst, row, src) in zip(arrays, writes):
+                B, H, rows, Dd = dst.shape
+                if (type(src) is not torch.Tensor or type(dst) is not torch.Tensor or Dd != D or src.shape != (B, H, D)
+                        or src.dtype is not dtype or dst.dtype is not dtype or src.get_device() != dev
+                        or dst.get_device() != dev or src.requires_grad or dst.requires_grad or src.is_neg()
+                        or dst.is_neg() or not 0 <= row < rows or not dst.is_contiguous()):
+                    break
+                s0, s1, s2 = src.stride()
+                if s2 != 1 or (B > 1 and s0 != H * s1):
+                    break
+                sp, stride = src.data_ptr(), s1 * d0.element_size()
+                dp = dst.data_ptr() + row * row_bytes
+                if (sp | stride | dp) & 15:
+                    break
+                a.src, a.dst, a.src_stride, a.dst_stride, a.heads = sp, dp, stride, rows * row_bytes, B * H
+            else:
+                _check(lib().bkv_append_rows(arrays, n, row_bytes, _stream()), "bkv_append_rows")
+                return
+    for dst, row, src in writes:
+        dst[:, :, row] = src
 
 
 # ---- Continual FPS -------------------------------------------------------------

@@ -469,10 +469,14 @@ __global__ __launch_bounds__(kStreamThreads) void fps_stream_kernel(const T* src
 // to kBatch) rows of its lanes' lowest bounds and take them against the
 // picks they miss.  Every value is the one the eager rule forms, whatever
 // the order, so the picks are the same.  On queries around centroids the
-// first 15 of 16 picks' cosines cost about two passes over the rows instead
-// of 15: 512 heads of 4096 x 128 bf16 rows take @NEW@ us, 1750 when every
-// pick re-read every row.  Bound by the three passes (1.6 GB; a head's 1 MB
-// does not stay in its XCD's L2) and, per pick, by a few dependent reads.
+// picks after the first cost about two passes over the rows instead of 15:
+// 512 heads of 4096 x 128 bf16 rows, 16 picks, take 481 us, 1750 when every
+// pick re-read every row.  162 us of it are the first two passes (6.6 TB/s;
+// the second runs backwards, so that it starts on rows still in the
+// memory-side cache) and 81 the third; the rest is the batches' reads, about
+// 1 GB at a few dependent reads per pick.  A batch's cosines with the picks
+// it misses are MFMA tiles of 16 rows by 16 picks; formed pick by pick on
+// the VALU the launch took 720 us.
 //
 // Rows are read by D * sizeof(T) / 16 lanes each, 16 bytes a lane (whole
 // lines, 1 KB per instruction); the vector a pass multiplies with sits in

@@ -155,17 +155,23 @@ class PeriodicEviction:
     def step(self, k, v, q_pre, q_rope):
         """One decoding step: k, v [LB, Hkv, D]; q_pre, q_rope [LB, Hq, D].
         Returns True when the step evicted."""
-        self.K[:, :, self.L] = k
-        self.V[:, :, self.L] = v
-        self.L += 1
+        # the step's rows: the token into the cache, its queries into the
+        # buffer (up to the freeze) or into the recent set (after it)
+        L, nb, nr = self.L + 1, self.nb, self.nr
+        writes = [(self.K, self.L, k), (self.V, self.L, v)]
+        recent = self.B_max - nr < L <= self.B_max
+        if recent:
+            writes += [(self.recent_rope, self.n_rec, q_rope), (self.recent_pre, self.n_rec, q_pre)]
+        elif self.mode == "beacon":
+            writes.append((self.obs, self.obs_len, q_pre))
+        bkv.append_rows(writes)
+        self.L = L
         self.t += 1
-        L, nb, nr = self.L, self.nb, self.nr
         if self.mode == "ns":
             q_new = q_pre.reshape(self.LB, self.Hq, 1, self.D).contiguous()
             self._call("beacon_update", lambda: bkv.beacon_update(self.dims, q_new, self.beacons, self.counts))
         if self.mode == "beacon":
             if L <= self.B_max - nr:
-                self.obs[:, :, self.obs_len] = q_pre
                 self.obs_len += 1
                 if self.obs_len >= nb + nr:
                     self._compress(self.obs_len, "fill")
@@ -177,9 +183,7 @@ class PeriodicEviction:
                     self.obs, nb, n=self.obs_len, dst=self.beacons.view(self.LB, self.Hq, nb, self.D),
                     counts=self.counts.view(self.LB, self.Hq, nb)))
                 self.n_rec = 0
-        if self.B_max - nr < L <= self.B_max:
-            self.recent_rope[:, :, self.n_rec] = q_rope
-            self.recent_pre[:, :, self.n_rec] = q_pre
+        if recent:
             self.n_rec += 1
         if L == self.B_max:
             self._evict()

@@ -229,3 +229,20 @@ def test_noalloc_rejects_dims_beyond_its_array():
     p = ctypes.c_void_p(16)  # any 16-byte aligned value: nothing is dereferenced on the host
     st = lib.bkv_evict_noalloc(ctypes.byref(big), 0, p, p, p, p, p, None, None, 0.0, None, None, None, None, None)
     assert st == bkv.ERR_WORKSPACE
+
+
+def test_append_rows_rejects():
+    def call(n=1, row_bytes=256, **kw):
+        r = (bkv.Rows * 1)(bkv.Rows(src=4096, dst=8192, src_stride=256, dst_stride=256, heads=0))
+        for k, v in kw.items():
+            setattr(r[0], k, v)
+        return bkv.lib().bkv_append_rows(r, n, row_bytes, None)
+
+    assert call() == bkv.OK and call(n=0) == bkv.OK  # nothing to write
+    assert call(n=5) == bkv.ERR_SHAPE and call(n=-1) == bkv.ERR_SHAPE
+    assert call(row_bytes=0) == bkv.ERR_SHAPE and call(row_bytes=24) == bkv.ERR_SHAPE
+    assert call(heads=-1) == bkv.ERR_SHAPE and call(heads=1 << 31) == bkv.ERR_SHAPE
+    assert call(heads=1 << 29) == bkv.ERR_SHAPE  # chunks past 32 bits
+    assert call(heads=1, src=None) == bkv.ERR_INVALID and call(heads=1, dst=None) == bkv.ERR_INVALID
+    for k in ("src", "dst", "src_stride", "dst_stride"):
+        assert call(heads=1, **{k: 4104}) == bkv.ERR_INVALID

@@ -24,6 +24,7 @@ import torch
 
 import oracle
 from gpu_util import assert_scores_close, compare_kept, host, say
+import paper_2609_04971_amd as bkv
 from paper_2609_04971_amd import synth
 from paper_2609_04971_amd.driver import PeriodicEviction
 
@@ -146,3 +147,25 @@ def test_periodic_eviction_lockstep_with_oracle():
         if whys[k] == "freeze":
             assert whys[k + 1] == "evict" and whys[k + 2] == "merge"
     assert "fill" in whys
+
+
+@pytest.mark.parametrize("dtype,D,rows", [(torch.bfloat16, 64, 3), (torch.float32, 128, 1), (torch.bfloat16, 128, 70)])
+def test_append_rows_equals_slice_assignment(dtype, D, rows):
+    # one launch for arrays of different head counts, the sources contiguous,
+    # strided by head, or (slice assignment) of another layout, dtype or device
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    new = lambda *s: torch.randn(*s, generator=g, device="cuda").to(dtype)
+    dst = [new(2, h, rows, D) for h in (8, 2, 4, 1)]
+    pool = new(2, 2, 5, D)
+    src = [new(2, 8, D), pool[:, :, 3], new(2, 4, D), new(2, 1, D)]
+    odd = [new(2, D, 8).transpose(1, 2), new(2, 2, D).double(), new(4, D), new(2, 1, D).cpu()]
+    for srcs in (src, odd, [odd[0]] + src[1:]):
+        want = [d.clone() for d in dst]
+        for i, (d, s) in enumerate(zip(want, srcs)):
+            d[:, :, (i * 7) % rows] = s
+        bkv.append_rows([(d, (i * 7) % rows, s) for i, (d, s) in enumerate(zip(dst, srcs))])
+        for d, x in zip(dst, want):
+            assert torch.equal(host(d), host(x))
+    with pytest.raises(IndexError):
+        bkv.append_rows([(dst[0], rows, src[0])])
+    bkv.append_rows([])
