@@ -87,6 +87,7 @@ _SIGS = {
     "bkv_score": ([_D, _P, _P, _P, _P, _P, _P, ctypes.c_float, _P, _P, _P, _S, _P], ctypes.c_int),
     "bkv_topk": ([_D, _P, _P, _P, _S, _P], ctypes.c_int),
     "bkv_compact": ([_D, _P, _P, _P, _P, _S, _P], ctypes.c_int),
+    "bkv_compact_fill": ([_D, _P, _P, _P, _P, _P, _S, _P], ctypes.c_int),
     "bkv_evict": ([_D, _P, _P, _P, _P, _P, _P, _P, ctypes.c_float, _P, _P, _P, _P, _S, _P], ctypes.c_int),
     "bkv_score_ex": ([_D, _I, _P, _P, _P, _P, _P, _P, ctypes.c_float, _P, _P, _P, _S, _P], ctypes.c_int),
     "bkv_evict_ex": ([_D, _I, _P, _P, _P, _P, _P, _P, _P, ctypes.c_float, _P, _P, _P, _P, _S, _P], ctypes.c_int),

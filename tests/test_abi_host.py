@@ -246,3 +246,8 @@ def test_append_rows_rejects():
     assert call(heads=1, src=None) == bkv.ERR_INVALID and call(heads=1, dst=None) == bkv.ERR_INVALID
     for k in ("src", "dst", "src_stride", "dst_stride"):
         assert call(heads=1, **{k: 4104}) == bkv.ERR_INVALID
+
+
+def test_every_export_has_a_signature():
+    # without one, ctypes passes an integer handle (a stream) as a C int
+    assert sorted(bkv._SIGS) == sorted(bkv.EXPORTS)
