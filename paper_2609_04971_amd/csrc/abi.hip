@@ -69,11 +69,10 @@ WsLayout ws_layout(const bkv_dims& d) {
         L.rtg = max(1, (tiles + nrg - 1) / nrg);
         L.R_pad_max = nrg * L.rtg * 16;
     }
-    // key chunk per score work item: 1024 keys once there are enough chunks
-    // to fill the machine about twice (shorter items spend their time on the
-    // ticket, the rows and the epilogue: at 4K tokens and 128 heads 1024-key
-    // items score 30 % faster than 256-key ones), or when the rows span
-    // several row groups (each group streams the chunk again); else 256
+    // Key chunk per score work item: 1024 keys once there are enough chunks
+    // to fill the machine about twice, or when the rows span several row
+    // groups (each group streams the chunk again); else 256.  The workspace
+    // holds the statistics of that many chunks.
     const long long big = (long long)P * ((d.N + 1023) / 1024);
     L.kgn = (big >= 512 || tiles > kFastTiles) ? 4 : 1;
     L.key_chunk = 256 * L.kgn;
@@ -82,6 +81,14 @@ WsLayout ws_layout(const bkv_dims& d) {
     off = align_up(off + sizeof(float) * (size_t)P * L.nch * L.R_pad_max);
     L.part_z = off;
     off = align_up(off + sizeof(float) * (size_t)P * L.nch * L.R_pad_max);
+    if (L.rtg > 0 && P > 0 && d.N > 0) {
+        // the fast path takes fewer, longer chunks (see kScoreSlots)
+        const bool multi = L.R_pad_max > L.rtg * 16;
+        const int longest = multi ? kMultiKeyChunk : kOneGroupKeyChunk;
+        const int n = min(L.nch, max(max(1, kScoreSlots / P), (d.N + longest - 1) / longest));
+        L.key_chunk = ((d.N + n - 1) / n + kKeyChunkUnit - 1) / kKeyChunkUnit * kKeyChunkUnit;
+        L.nch = (d.N + L.key_chunk - 1) / L.key_chunk;
+    }
     L.lse2 = off;
     off = align_up(off + sizeof(float) * (size_t)P * L.R_pad_max);
     L.rows = off;

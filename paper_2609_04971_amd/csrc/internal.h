@@ -79,6 +79,26 @@ struct WsLayout {
 // The score fast path (bf16) holds the rows of one row group in registers:
 // at most kFastTiles tiles per group and kFastRowGroups groups.
 constexpr int kFastTiles = 9;
+// The fast path's key chunks (work items).  A chunk costs about as much
+// around its key loop (ticket, rows, count-in, hand-off) as 600 keys in it,
+// so chunks are as long as LDS and the balance of the machine allow: as many
+// as fill the compute units' two workgroups each (kScoreSlots items), and
+// more only so that none is longer than the limits below.  Measured with R =
+// 144 against chunks of 1024 keys (256 with fewer than 512 such chunks), us:
+//   heads x keys    before  chunks a head, after
+//   4608 x 4224     1882    3   1789
+//   256 x 16384     430     10   376 (chunks of 2^10 keys also start all
+//   128 x 32768     402     20   371  streams on the same memory channels)
+//   128 x 4224      76.6    4    65.9
+//   128 x 2048      62.8    4    47.6 (2 chunks: 54.8, 8: 62.8)
+//   64 x 4096       59.4    8    47.1 (4: 54.3, 16: 58.8)
+//   8 x 32768       66.2    64   46.7 (32: 57.0, 128: 67.1)
+//   256 x 1024      62.6    2    46.6
+// and for four row groups 32 x 65536: 578, 47 chunks 526.
+constexpr int kOneGroupKeyChunk = 1664;
+constexpr int kMultiKeyChunk = 1408;  // several row groups: two values per key in LDS
+constexpr int kKeyChunkUnit = 128;    // four waves of 32-key groups
+constexpr int kScoreSlots = 512;
 
 // Split selection: words per head, slices per head at most, heads at most
 // for which the regions are laid out, and the shortest head it takes.
@@ -112,7 +132,7 @@ hipError_t launch_score(const bkv_dims& d, const WsLayout& L, int flags, const v
 
 // The whole eviction in one launch (score, select and compact work items
 // under one per-head ticket); only where evict_fusable (the bf16 fast path,
-// heads of 16K to 32K tokens, where it measured at least as fast as the
+// large layers of 16K to 32K tokens, where it measured faster than the
 // chained launches).  kept and scores are required (the workspace's own may
 // be passed).
 bool evict_fusable(const bkv_dims& d, const WsLayout& L);

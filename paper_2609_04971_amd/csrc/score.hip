@@ -678,8 +678,11 @@ struct alignas(16) StageBuf {
     uint16_t k[kWaves][KeyStage<D>::ELEMS];
 };
 
-constexpr int kMaxKeyChunk = 1024;  // keys per work item at most
+// Keys per work item at most (the layout's choice is L.key_chunk): one row
+// group keeps one value per key in LDS, several keep two.
+constexpr int max_key_chunk(bool multi) { return multi ? kMultiKeyChunk : kOneGroupKeyChunk; }
 
+template <bool MULTI>
 struct alignas(16) FastSmem {
     union {
         struct {
@@ -687,9 +690,9 @@ struct alignas(16) FastSmem {
             float z[kWaves][kFRT * 16];
         } red;  // S items: per-wave row statistics
         struct {
-            float nlse[kFRT * 16];      // -lse of each row (raw-dot units)
-            float kacc[kMaxKeyChunk];   // each key's result (with several row groups: so far)
-            float kaccs[kMaxKeyChunk];  // mean form, several row groups: each key's weight sum so far
+            float nlse[kFRT * 16];              // -lse of each row (raw-dot units)
+            float kacc[max_key_chunk(MULTI)];   // each key's result (with several row groups: so far)
+            float kaccs[MULTI ? max_key_chunk(MULTI) : 1];  // mean form, several row groups: each key's weight sum so far
         } fin;  // F items
     } v;
     int lim[kFRT * 16];  // last key each row sees (KeyMask::limit)
@@ -1163,7 +1166,7 @@ __device__ __forceinline__ void wait_group(bool more) {
 // MULTI: the rows come in several row groups, each loaded here (else the
 // item's only group was loaded with its ticket).
 template <int D, int RT, bool MULTI>
-__device__ __forceinline__ void fast_stats(const Args& a, int h, int chunk, FastSmem& sm, StageBuf<D>& sa, StageBuf<D>& sb,
+__device__ __forceinline__ void fast_stats(const Args& a, int h, int chunk, FastSmem<MULTI>& sm, StageBuf<D>& sa, StageBuf<D>& sb,
                            Op<uint16_t, D>* yr, int* s_flag) {
     const int KC = a.key_chunk, KPW = KC / kWaves, GPW = KPW / kFKG;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -1307,7 +1310,7 @@ __device__ __forceinline__ void final_loop(const uint16_t* Kh, int kw, int ngrou
 }
 
 template <int D, int RT, bool MULTI>
-__device__ __forceinline__ void fast_final(const Args& a, int h, int chunk, FastSmem& sm, StageBuf<D>& sa, StageBuf<D>& sb,
+__device__ __forceinline__ void fast_final(const Args& a, int h, int chunk, FastSmem<MULTI>& sm, StageBuf<D>& sa, StageBuf<D>& sb,
                            Op<uint16_t, D>* yr, int* s_flag) {
     const int KC = a.key_chunk, KPW = KC / kWaves, GPW = KPW / kFKG;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -1381,12 +1384,12 @@ __device__ __forceinline__ void fast_final(const Args& a, int h, int chunk, Fast
 // form) meet each key's maximum across the waves with an LDS atomic max.
 constexpr int kSplitGroups = 4;
 constexpr int kSuper = kWaves * kFKG;  // keys per super-stage
-static_assert(kSplitGroups == kWaves && kMaxKeyChunk % kSuper == 0, "one row group per wave");
+static_assert(kSplitGroups == kWaves && kMultiKeyChunk % kSuper == 0, "one row group per wave");
 
 struct SplitLds {  // overlays FastSmem::v (S items use lim only)
     int lim[kSplitGroups][kFRT * 16];
     float nlse[kSplitGroups][kFRT * 16];
-    unsigned kmax[kMaxKeyChunk];
+    unsigned kmax[kMultiKeyChunk];
 };
 
 // Issue super-stage s of an item (keys k0 + s kSuper ...): wave w loads its group.
@@ -1398,9 +1401,9 @@ __device__ __forceinline__ void issue_super(const uint16_t* Kh, int k0, int s, i
 }
 
 template <int D, int RT>
-__device__ void split_stats(const Args& a, int h, int chunk, FastSmem& sm, StageBuf<D>& sa, StageBuf<D>& sb,
+__device__ void split_stats(const Args& a, int h, int chunk, FastSmem<true>& sm, StageBuf<D>& sa, StageBuf<D>& sb,
                             int* s_flag) {
-    static_assert(sizeof(SplitLds) <= sizeof(FastSmem::v), "row-split LDS fits the overlay");
+    static_assert(sizeof(SplitLds) <= sizeof(FastSmem<true>::v), "row-split LDS fits the overlay");
     SplitLds& sl = *reinterpret_cast<SplitLds*>(&sm.v);
     const int KC = a.key_chunk;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -1501,7 +1504,7 @@ __device__ void split_stats(const Args& a, int h, int chunk, FastSmem& sm, Stage
 }
 
 template <int D, int RT>
-__device__ void split_final(const Args& a, int h, int chunk, FastSmem& sm, StageBuf<D>& sa, StageBuf<D>& sb,
+__device__ void split_final(const Args& a, int h, int chunk, FastSmem<true>& sm, StageBuf<D>& sa, StageBuf<D>& sb,
                             int* s_flag) {
     SplitLds& sl = *reinterpret_cast<SplitLds*>(&sm.v);
     const int KC = a.key_chunk;
@@ -1576,7 +1579,7 @@ __device__ void split_final(const Args& a, int h, int chunk, FastSmem& sm, Stage
 // S or F item of a row-split head (F items of the mean form take the
 // row-group loop: their per-key (max, sum) pairs do not merge by atomics).
 template <int D, int RT>
-__device__ __forceinline__ void split_item(const Args& a, int h, int ticket, FastSmem& sm, StageBuf<D>& sa,
+__device__ __forceinline__ void split_item(const Args& a, int h, int ticket, FastSmem<true>& sm, StageBuf<D>& sa,
                                            StageBuf<D>& sb, int* s_flag) {
     if (ticket < a.nch) {
         split_stats<D, RT>(a, h, ticket, sm, sa, sb, s_flag);
@@ -1591,7 +1594,7 @@ __device__ __forceinline__ void split_item(const Args& a, int h, int ticket, Fas
 // SPLIT: four row groups, one per wave (MULTI is then true as well).
 template <int D, int RT, bool MULTI, bool SPLIT>
 __global__ __launch_bounds__(kThreads, 2) void fast_score_kernel(Args a) {
-    __shared__ FastSmem sm;
+    __shared__ FastSmem<MULTI> sm;
     __shared__ StageBuf<D> sa;
     __shared__ StageBuf<D> sb;
     __shared__ int s_ticket, s_ok, s_flag;
@@ -1655,7 +1658,7 @@ __device__ __forceinline__ int head_of_block_fused(const Args& a, int b) {
 
 template <int D, int RT, bool MULTI, bool SPLIT>
 __global__ __launch_bounds__(kThreads, 2) void evict_kernel(Args a) {
-    __shared__ FastSmem sm;
+    __shared__ FastSmem<MULTI> sm;
     __shared__ StageBuf<D> sa;
     __shared__ StageBuf<D> sb;
     __shared__ int s_ticket, s_ok, s_flag;
@@ -1730,7 +1733,7 @@ hipError_t launch_fast_rt(const Args& a, hipStream_t s) {
     const bool multi = a.R_pad_max > RT * 16;
     // four row groups of 7 to 9 tiles (R of about 400 to 576): one per wave
     if constexpr (RT >= 7) {
-        if (a.R_pad_max == kSplitGroups * RT * 16 && a.key_chunk == kMaxKeyChunk) {
+        if (a.R_pad_max == kSplitGroups * RT * 16 && a.key_chunk <= kMultiKeyChunk) {
             if (a.fused)
                 hipLaunchKernelGGL((evict_kernel<D, RT, true, true>), dim3(a.total), dim3(kThreads), 0, s, a);
             else
@@ -1847,7 +1850,10 @@ hipError_t launch_score_impl(const bkv_dims& d, const WsLayout& L, int flags, co
     if (hipGetDevice(&dev_id) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev_id) != hipSuccess)
         cus = 256;
-    int lag = (4 * cus + 2 * L.nch - 1) / (2 * L.nch);
+    // The fused launch, whose compaction items run behind, takes 0.6 of that:
+    // 24K layers 388 -> 377 us, 16K 275 -> 267, 32K the same.
+    const int lag_items = V ? 12 * cus / 5 : 4 * cus;
+    int lag = (lag_items + 2 * L.nch - 1) / (2 * L.nch);
     a.lag = lag < 1 ? 1 : (lag > L.P ? L.P : lag);
     a.total = 2 * L.P * L.nch;
     a.tickets = 2 * L.nch;
@@ -1898,14 +1904,20 @@ hipError_t launch_score(const bkv_dims& d, const WsLayout& L, int flags, const v
                              row_lse, nullptr, ws, s);
 }
 
-// Shorter heads have few score items per head, so the selection and
-// compaction items come at the end of the grid and run with little to
-// overlap (the 4224-token steady state measured 217 us fused against 210
-// chained); longer heads take the selection's streaming path; heads of
-// several row groups leave the score items long and few (the R = 464 16K
-// layer measured 293 us fused against 213 chained).
+// Where one launch is ahead of the three chained ones (us, one row group of
+// 144): 128 heads of 32768 tokens down to 4096 450 against 493, 64 such heads
+// 247 against 282, 128 of 16400 267 against 276.  Not ahead, so chained:
+// shorter heads, whose selection and compaction come at the end of the grid
+// with little to overlap (128 of 14000 255 against 247, of 8192 193 against
+// 150); few heads, whose selection is one workgroup each (48 of 17000 157
+// against 145, 32 of 16384 133 against 100, 8 of 16384 97 against 63; the
+// split selection serves them); evictions that keep most of the cache, whose
+// compaction wants the whole machine (28672 of 32768 tokens 1240 against
+// 1056; half of them 755 against 770); heads past 32768 tokens (the
+// selection's streaming path) and of several row groups.
 bool evict_fusable(const bkv_dims& d, const WsLayout& L) {
-    return L.rtg > 0 && L.R_pad_max == L.rtg * 16 && L.nch >= 16 && d.N <= 32768;
+    return L.rtg > 0 && L.R_pad_max == L.rtg * 16 && d.N > 15360 && d.N <= 32768 &&
+           (long long)L.P * d.N >= 1500000 && 2LL * d.budget <= d.N;
 }
 
 hipError_t launch_evict_fused(const bkv_dims& d, const WsLayout& L, int flags, void* K, void* V, const void* q_win,

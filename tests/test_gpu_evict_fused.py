@@ -128,3 +128,38 @@ def test_fused_evict_bulk_ties(distinct):
     d = dims_of(w)
     say(f"fused evict with {distinct} distinct keys {d}")
     _check(w, x, d, seed_note=f"{distinct} distinct: ")
+
+
+# The fused launch takes layers of 1.5 million tokens or more that keep at
+# most half of them; the small cases above now go through the chained calls
+# inside bkv_evict.  96 heads or so of one query head each reach every part
+# of it: ragged tails, the prefix, D = 64, budgets above the selection's bin
+# count, chunks of unequal length, the options, and bulk ties.
+FUSED = {
+    "ragged-prefix": (W("g1", B=12, Hq=8, Hkv=8, D=128, N=16391, W=16, C=8, budget=2000, n_prefix=5), False, False),
+    "d64-causal": (W("g2", B=13, Hq=8, Hkv=8, D=64, N=15999, W=9, C=3, budget=2048), False, True),
+    "half-kept-mean": (W("g3", B=6, Hq=8, Hkv=8, D=128, N=32768, W=16, C=8, budget=16384), True, False),
+    "nine-tiles": (W("g4", B=12, Hq=32, Hkv=8, D=128, N=17003, W=32, C=16, budget=1000, revisit_frac=0.05), True, True),
+}
+
+
+@pytest.mark.parametrize("name", list(FUSED))
+def test_fused_launch_on_large_layers(name):
+    w, mean, causal = FUSED[name]
+    x = {k: host(v) for k, v in synth.make_layer(w, seed=75, device="cuda").items()}
+    d = dims_of(w)
+    say(f"fused launch {name} {d}")
+    _check(w, x, d, mean, causal)
+
+
+@pytest.mark.parametrize("distinct", [1, 3, 40])
+def test_fused_launch_bulk_ties(distinct):
+    w = W("g5", B=12, Hq=8, Hkv=8, D=64, N=16500, W=16, C=4, budget=2100, n_prefix=2)
+    x = synth.make_layer(w, seed=76, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(77)
+    pick = torch.randint(0, distinct, (w.B, w.Hkv, w.N), generator=g, device="cuda")
+    x["K"] = torch.gather(x["K"][:, :, :distinct], 2, pick.unsqueeze(-1).expand(-1, -1, -1, w.D))
+    x = {k: host(v) for k, v in x.items()}
+    d = dims_of(w)
+    say(f"fused launch with {distinct} distinct keys {d}")
+    _check(w, x, d, seed_note=f"{distinct} distinct: ")

@@ -202,3 +202,40 @@ def test_score_key_far_above_its_lanes_first_keys(mean):
     err = assert_scores_close(host(scores).numpy(), s_ref)
     assert_scores_close(host(lse).numpy(), lse_ref, "row_lse")
     say(f"  max |diff| {err:.2e}")
+
+
+# Key chunks: the longest of one and of several row groups (1664 and 1408
+# keys) and one key more, chunks that end inside a wave's 32-key group or
+# leave waves without keys, and few heads (the shortest chunks).
+CHUNK_CASES = [  # B, Hkv, G, D, N, W, C, mean, causal
+    (33, 16, 1, 128, 1664, 8, 4, False, True), (33, 16, 1, 128, 1665, 8, 4, True, False), (33, 16, 1, 64, 1537, 16, 0, False, False),
+    (65, 8, 1, 128, 127, 4, 3, False, True), (65, 8, 1, 64, 33, 4, 3, True, True), (16, 8, 4, 128, 4223, 32, 16, False, False),
+    (33, 8, 7, 128, 1408, 64, 16, False, True), (33, 8, 7, 64, 1409, 64, 16, True, False), (33, 8, 5, 128, 1407, 40, 8, True, True),
+    (1, 2, 4, 128, 2049, 32, 16, False, False), (1, 1, 8, 128, 5000, 64, 16, False, True)]
+
+
+@pytest.mark.parametrize("case", CHUNK_CASES)
+def test_score_key_chunks(case):
+    import paper_2609_04971_amd as bkv
+    B, Hkv, G, D, N, Wn, C, mean, causal = case
+    w = W("chunk", B=B, Hq=Hkv * G, Hkv=Hkv, D=D, N=N, W=Wn, C=C, budget=64, revisit_frac=0.1)
+    x = synth.make_layer(w, seed=N + D, N_cap=N + 3)
+    if C > 2:
+        x["counts"][:, :, 1] = 0  # empty slots: the occupied ones are listed past them
+    x["K"][:, :, N:] = float("nan")  # rows past N are never scored
+    d = dims_of(w, N_cap=N + 3)
+    ws = bkv.workspace(d, bkv.OP_SCORE)
+    scores = torch.full((B, Hkv, N), float("nan"), device="cuda")
+    lse = torch.full((B, Hkv, C + G * Wn), float("nan"), device="cuda")
+    xd = to_dev(x)
+    bkv.score(d, xd["K"], xd["q_win"], xd["beacons"], xd["counts"], scores, ws, row_lse=lse, rope_cos=xd["rope_cos"],
+              rope_sin=xd["rope_sin"], mean=mean, causal=causal)
+    assert bkv.device_status(ws) == bkv.OK
+    heads = [(b, h) for b in sorted({0, B - 1}) for h in sorted({0, Hkv - 1})]
+    s_ref, lse_ref = oracle.score(x["K"], x["q_win"], x["beacons"], x["counts"], N=N, rope_cos=x["rope_cos"],
+                                  rope_sin=x["rope_sin"], heads=heads, threads=8, agg="mean" if mean else "max",
+                                  causal=causal)
+    sel = tuple(np.array(heads).T)
+    assert_scores_close(host(scores).numpy()[sel], s_ref[sel])
+    assert_scores_close(host(lse).numpy()[sel], lse_ref[sel], "row_lse")
+    assert not torch.isnan(scores).any()
