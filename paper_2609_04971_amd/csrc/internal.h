@@ -73,6 +73,7 @@ struct WsLayout {
     size_t kept;            // evict: kept indices when the caller passes none [P][budget]
     size_t evict_end;
     int P, nseg, R_pad_max, nch, kgn, key_chunk;
+    int nch_ws;  // score chunks per head whose statistics the workspace holds
     int rtg;  // score fast path: row tiles (16 rows) per row group; 0 selects the generic path
 };
 
@@ -94,11 +95,18 @@ constexpr int kFastTiles = 9;
 //   64 x 4096       59.4    8    47.1 (4: 54.3, 16: 58.8)
 //   8 x 32768       66.2    64   46.7 (32: 57.0, 128: 67.1)
 //   256 x 1024      62.6    2    46.6
-// and for four row groups 32 x 65536: 578, 47 chunks 526.
+// and for four row groups 32 x 65536: 578, 47 chunks 526.  Heads of several
+// row groups, whose items are longer, like a few more of them (640: 32 x
+// 12345 of 192 rows 100 -> 87 us with 20 chunks a head against 13, 97 with
+// 14; 32 x 16384 of 464 rows 134 -> 128 with 20 against 16; 64 x 12000 of
+// 320 rows 144 with 10, 135 with 8), unless there are so many heads that the
+// count a head gets is the coarse one (128 x 4096: 4 chunks 127, 5 145).
 constexpr int kOneGroupKeyChunk = 1664;
 constexpr int kMultiKeyChunk = 1408;  // several row groups: two values per key in LDS
 constexpr int kKeyChunkUnit = 128;    // four waves of 32-key groups
 constexpr int kScoreSlots = 512;
+constexpr int kMultiScoreItems = 640;
+constexpr int kMultiHeads = 64;
 
 // Split selection: words per head, slices per head at most, heads at most
 // for which the regions are laid out, and the shortest head it takes.

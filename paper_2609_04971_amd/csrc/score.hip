@@ -88,8 +88,9 @@ struct Args {
     float* row_lse;
     int* hdr;
     int* hctl;      // [P][kHcWords] per-head control lines
-    float* part_m;  // [P][nch][R_pad_max] chunk row maxima (log2 units)
-    float* part_z;  // [P][nch][R_pad_max] chunk row sums relative to part_m
+    float* part_m;  // per head (part_head floats apart) [nch][R_pad_max] chunk row maxima (log2 units)
+    float* part_z;  // likewise, chunk row sums relative to part_m
+    size_t part_head;
     float* lse2;    // [P][R_pad_max] row log2-normalisers
     uint16_t* rows; // [P][R_pad_max / 16][NV][64] observation rows, one MFMA operand vector per lane
     int* rmeta;     // [P][kMetaWords] occupied beacon slots of each head
@@ -295,7 +296,7 @@ __device__ void build_rows(const Args& a, int h, int r0, int nr, const int* act,
 __device__ void fold_and_publish(const Args& a, int h, const int* act, int nact, int* hc) {
     const int tid = threadIdx.x;
     const int R = nact + a.G * a.W;
-    const size_t hb = (size_t)h * a.nch * a.R_pad_max;
+    const size_t hb = (size_t)h * a.part_head;
     for (int r = tid; r < a.R_pad_max; r += kThreads) {
         float mm = -INFINITY, zz = 0.f;
         if (r < R) {
@@ -375,7 +376,7 @@ __device__ void stats_item(const Args& a, int h, int chunk, Smem<T, D>& sm, int*
     const int kw = chunk * KC + wave * 64 * KGN;  // this wave's first key
     const int N = a.N;
     const float s2 = a.s2;
-    const size_t pbase = ((size_t)h * a.nch + chunk) * a.R_pad_max;
+    const size_t pbase = (size_t)h * a.part_head + (size_t)chunk * a.R_pad_max;
     const KeyMask mk = key_mask(a, nact);
 
     for (int r0 = 0; r0 < Rp; r0 += RG) {
@@ -1185,7 +1186,7 @@ __device__ __forceinline__ void fast_stats(const Args& a, int h, int chunk, Fast
     const float s2 = a.s2;
     const KeyMask mk = key_mask(a, a.rmeta[(size_t)h * kMetaWords]);
     const int clear_below = mk.all_see_below();
-    const size_t pbase = ((size_t)h * a.nch + chunk) * a.R_pad_max;
+    const size_t pbase = (size_t)h * a.part_head + (size_t)chunk * a.R_pad_max;
     // Rows in groups of 16 RT; the chunk's keys are streamed again for every
     // further group.
     const int nrg = MULTI ? a.R_pad_max / (RT * 16) : 1;
@@ -1487,7 +1488,7 @@ __device__ void split_stats(const Args& a, int h, int chunk, FastSmem<true>& sm,
 #pragma unroll
     for (int i = 0; i < RT; ++i) normalise_mz(m[i], z[i]);
     // this wave's rows: lanes sharing a row (g = 0..3) meet, then go out
-    const size_t pbase = ((size_t)h * a.nch + chunk) * a.R_pad_max + (size_t)wave * RT * 16;
+    const size_t pbase = (size_t)h * a.part_head + (size_t)chunk * a.R_pad_max + (size_t)wave * RT * 16;
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
         merge_mz(m[rt], z[rt], dev::shfl_xor_f(m[rt], 16), dev::shfl_xor_f(z[rt], 16));
@@ -1827,6 +1828,15 @@ hipError_t launch_score_impl(const bkv_dims& d, const WsLayout& L, int flags, co
     a.hctl = reinterpret_cast<int*>(w + L.hctl);
     a.part_m = reinterpret_cast<float*>(w + L.part_m);
     a.part_z = reinterpret_cast<float*>(w + L.part_z);
+    a.part_head = (size_t)L.nch * L.R_pad_max;
+    if (L.nch > L.nch_ws) {
+        // more chunks than the workspace has room for: a head's statistics
+        // go where its scores will (they fit, see the layout).  Its F items
+        // write those only after the fold has read every statistic.
+        a.part_m = scores;
+        a.part_z = scores + a.part_head;
+        a.part_head = d.N;
+    }
     a.lse2 = reinterpret_cast<float*>(w + L.lse2);
     a.B = d.B;
     a.Hq = d.Hq;

@@ -211,7 +211,10 @@ CHUNK_CASES = [  # B, Hkv, G, D, N, W, C, mean, causal
     (33, 16, 1, 128, 1664, 8, 4, False, True), (33, 16, 1, 128, 1665, 8, 4, True, False), (33, 16, 1, 64, 1537, 16, 0, False, False),
     (65, 8, 1, 128, 127, 4, 3, False, True), (65, 8, 1, 64, 33, 4, 3, True, True), (16, 8, 4, 128, 4223, 32, 16, False, False),
     (33, 8, 7, 128, 1408, 64, 16, False, True), (33, 8, 7, 64, 1409, 64, 16, True, False), (33, 8, 5, 128, 1407, 40, 8, True, True),
-    (1, 2, 4, 128, 2049, 32, 16, False, False), (1, 1, 8, 128, 5000, 64, 16, False, True)]
+    (1, 2, 4, 128, 2049, 32, 16, False, False), (1, 1, 8, 128, 5000, 64, 16, False, True),
+    # chunk statistics laid where the scores will be: exactly full, one short, 20 chunks a head, odd N
+    (1, 2, 4, 128, 1920, 32, 16, False, True), (1, 2, 4, 128, 1919, 32, 16, True, False),
+    (4, 8, 4, 128, 12345, 32, 16, False, True), (3, 3, 5, 64, 9001, 33, 7, True, True)]
 
 
 @pytest.mark.parametrize("case", CHUNK_CASES)
