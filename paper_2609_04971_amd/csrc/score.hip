@@ -465,10 +465,14 @@ __device__ void final_item(const Args& a, int h, int chunk, Smem<T, D>& sm, int*
     constexpr int KC = kWaves * 64 * KGN;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int g = lane >> 4, c16 = lane & 15;
-    if (!await_lse(a, h, s_flag)) return;
+    // The first rows are built before the head's normalisers are awaited:
+    // short heads are bound by the chain S items -> fold -> F items, and the
+    // build is off it (fp32, 2 x 512, 68 rows: eviction 55.7 -> 54.5 us).
     active_slots(a, h, sm.act, &sm.nact);
     const int R = sm.nact + a.G * a.W;
     const int Rp = (R + 15) & ~15;
+    build_rows<T, D, LD>(a, h, 0, min(RG, Rp), sm.act, sm.nact, sm.y);
+    if (!await_lse(a, h, s_flag)) return;
     const T* Kh = reinterpret_cast<const T*>(a.K) + (size_t)h * a.N_cap * D;
     const int k0 = chunk * KC;
     const int kw = k0 + wave * 64 * KGN;
@@ -485,7 +489,7 @@ __device__ void final_item(const Args& a, int h, int chunk, Smem<T, D>& sm, int*
     for (int r0 = 0; r0 < Rp; r0 += RG) {
         const int nr = min(RG, Rp - r0), RT = nr / 16;
         __syncthreads();
-        build_rows<T, D, LD>(a, h, r0, nr, sm.act, sm.nact, sm.y);
+        if (r0 > 0) build_rows<T, D, LD>(a, h, r0, nr, sm.act, sm.nact, sm.y);
         for (int r = tid; r < nr; r += kThreads)
             sm.nlse[r] = -dev::ld_coherent(a.lse2 + (size_t)h * a.R_pad_max + r0 + r) * inv_s2;
         __syncthreads();
