@@ -23,6 +23,11 @@
 // lanes update that slot's D coordinates and its norm in parallel.  Finally
 // the changed slots are written back (at most T*G of the C rows; the others
 // still hold what was read).  The LDS is sized by C.
+//
+// Calls that bring many queries per head (prompts) take beacon_batch_kernel
+// instead, which forms the cosines of 16 queries with every slot and with
+// each other on the matrix cores and keeps only the assignments serial; its
+// results are the same, bit for bit (see there for the rule and why).
 #include <math.h>
 
 #include "device_common.h"

@@ -25,10 +25,10 @@
 //
 // The three larger kernels use the regrouped average
 //     sum_j cos(q_i, q_j) = (q_i / |q_i|) . sum_j (q_j / |q_j|),
-// which is O(n D) instead of O(n^2 D).  All four take the lowest index among equal values at every argmin, treat a
-// zero vector as having cosine 0 with everything, and emit the picks in
-// selection order.  The 1/n of avg_i is left out: it does not move the
-// argmin.
+// which is O(n D) instead of O(n^2 D).  All four take the lowest index among
+// equal values at every argmin, treat a zero vector as having cosine 0 with
+// everything, and emit the picks in selection order.  The 1/n of avg_i is
+// left out: it does not move the argmin.
 #include <math.h>
 
 #include "device_common.h"

@@ -95,17 +95,23 @@ constexpr int kFastTiles = 9;
 //   64 x 4096       59.4    8    47.1 (4: 54.3, 16: 58.8)
 //   8 x 32768       66.2    64   46.7 (32: 57.0, 128: 67.1)
 //   256 x 1024      62.6    2    46.6
-// and for four row groups 32 x 65536: 578, 47 chunks 526.  Heads of several
-// row groups, whose items are longer, like a few more of them (640: 32 x
-// 12345 of 192 rows 100 -> 87 us with 20 chunks a head against 13, 97 with
-// 14; 32 x 16384 of 464 rows 134 -> 128 with 20 against 16; 64 x 12000 of
-// 320 rows 144 with 10, 135 with 8), unless there are so many heads that the
-// count a head gets is the coarse one (128 x 4096: 4 chunks 127, 5 145).
+// Heads of several row groups take shorter chunks and more of them (192 to
+// 544 rows, us by chunks a head; those taken are marked):
+//   32 x 65536   47  585   52  582   57* 549   64  551
+//   128 x 16384  12  509   13  493   15* 492   16  515
+//   64 x 12000   9   151   10  148   11  142   12* 136   16  136
+//   40 x 20000   15  146   16  139   18* 139   24  139
+//   32 x 12345   13  102   14  97    18  91    20* 86    25  89
+//   96 x 6000    5   165   6*  151
+//   128 x 4224   3   162   4*  136   5   151
+// which is chunks of at most 1152 keys, and kMultiScoreItems of them in all
+// unless there are so many heads that the count a head gets would be a
+// coarse one (128 x 4096: 4 chunks 127, 5 145, 6 143).
 constexpr int kOneGroupKeyChunk = 1664;
-constexpr int kMultiKeyChunk = 1408;  // several row groups: two values per key in LDS
+constexpr int kMultiKeyChunk = 1152;  // several row groups
 constexpr int kKeyChunkUnit = 128;    // four waves of 32-key groups
 constexpr int kScoreSlots = 512;
-constexpr int kMultiScoreItems = 640;
+constexpr int kMultiScoreItems = 768;
 constexpr int kMultiHeads = 64;
 
 // Split selection: words per head, slices per head at most, heads at most

@@ -204,13 +204,13 @@ def test_score_key_far_above_its_lanes_first_keys(mean):
     say(f"  max |diff| {err:.2e}")
 
 
-# Key chunks: the longest of one and of several row groups (1664 and 1408
+# Key chunks: the longest of one and of several row groups (1664 and 1152
 # keys) and one key more, chunks that end inside a wave's 32-key group or
 # leave waves without keys, and few heads (the shortest chunks).
 CHUNK_CASES = [  # B, Hkv, G, D, N, W, C, mean, causal
     (33, 16, 1, 128, 1664, 8, 4, False, True), (33, 16, 1, 128, 1665, 8, 4, True, False), (33, 16, 1, 64, 1537, 16, 0, False, False),
     (65, 8, 1, 128, 127, 4, 3, False, True), (65, 8, 1, 64, 33, 4, 3, True, True), (16, 8, 4, 128, 4223, 32, 16, False, False),
-    (33, 8, 7, 128, 1408, 64, 16, False, True), (33, 8, 7, 64, 1409, 64, 16, True, False), (33, 8, 5, 128, 1407, 40, 8, True, True),
+    (33, 8, 7, 128, 1152, 64, 16, False, True), (33, 8, 7, 64, 1153, 64, 16, True, False), (33, 8, 5, 128, 1151, 40, 8, True, True),
     (1, 2, 4, 128, 2049, 32, 16, False, False), (1, 1, 8, 128, 5000, 64, 16, False, True),
     # chunk statistics laid where the scores will be: exactly full, one short, 20 chunks a head, odd N
     (1, 2, 4, 128, 1920, 32, 16, False, True), (1, 2, 4, 128, 1919, 32, 16, True, False),
