@@ -85,12 +85,14 @@ WsLayout ws_layout(const bkv_dims& d) {
     if (L.rtg > 0 && P > 0 && d.N > 0) {
         // the fast path splits its heads evenly (see kScoreSlots)
         const bool multi = L.R_pad_max > L.rtg * 16;
-        const int longest = multi ? kMultiKeyChunk : kOneGroupKeyChunk;
         // statistics past the workspace's room can go where the head's scores
         // will: two values per row and chunk, one score per token
         const int room = max(L.nch_ws, d.N / (2 * L.R_pad_max));
-        const int n = min(room, max(max(1, (multi && P <= kMultiHeads ? kMultiScoreItems : kScoreSlots) / P), (d.N + longest - 1) / longest));
-        L.key_chunk = ((d.N + n - 1) / n + kKeyChunkUnit - 1) / kKeyChunkUnit * kKeyChunkUnit;
+        const int items = multi && P <= kMultiHeads ? kMultiScoreItems : kScoreSlots;
+        const bool few = (long long)P * d.N < kFewTokens;
+        const int longest = multi ? kMultiKeyChunk : few ? kFewKeyChunk : kOneGroupKeyChunk;
+        const int n = min(room, max(max(1, items / P), (d.N + longest - 1) / longest));
+        L.key_chunk = max(kShortKeyChunk, ((d.N + n - 1) / n + kKeyChunkUnit - 1) / kKeyChunkUnit * kKeyChunkUnit);
         L.nch = (d.N + L.key_chunk - 1) / L.key_chunk;
     }
     L.lse2 = off;

@@ -95,6 +95,18 @@ constexpr int kFastTiles = 9;
 //   64 x 4096       59.4    8    47.1 (4: 54.3, 16: 58.8)
 //   8 x 32768       66.2    64   46.7 (32: 57.0, 128: 67.1)
 //   256 x 1024      62.6    2    46.6
+// A layer of few tokens runs only a few rounds of items, so its last round
+// counts for more than what an item costs around its loop: it takes chunks of
+// at most 1152 keys (chunks a head, us, by row count; * the one taken):
+//   66 x 12520, 48 rows    8  83    10  77    11* 76   13  76
+//   48 x 30000, 48 rows    18 121   24  116   27* 116
+//   148 x 5440, 48 rows    4  78    5*  74    6   74
+//   100 x 6000, 144 rows   5  79    6*  74
+//   100 x 17472, 96 rows   11 150   15  145   16* 147
+//   and past that line  200 x 9000, 144 rows: 6* 174, 8 184, 9 177;
+//   168 x 13617, 144 rows: 9* 215, 12 219, 14 220
+// A chunk is at least 256 keys (60 x 486, 56 rows: 1 chunk 21.4, 2* 19.1,
+// 4 19.5).
 // Heads of several row groups take shorter chunks and more of them (192 to
 // 544 rows, us by chunks a head; those taken are marked):
 //   32 x 65536   47  585   52  582   57* 549   64  551
@@ -108,6 +120,9 @@ constexpr int kFastTiles = 9;
 // unless there are so many heads that the count a head gets would be a
 // coarse one (128 x 4096: 4 chunks 127, 5 145, 6 143).
 constexpr int kOneGroupKeyChunk = 1664;
+constexpr int kFewKeyChunk = 1152;    // one row group, fewer than kFewTokens tokens in all
+constexpr long long kFewTokens = 1750000;
+constexpr int kShortKeyChunk = 256;
 constexpr int kMultiKeyChunk = 1152;  // several row groups
 constexpr int kKeyChunkUnit = 128;    // four waves of 32-key groups
 constexpr int kScoreSlots = 512;

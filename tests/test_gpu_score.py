@@ -214,7 +214,9 @@ CHUNK_CASES = [  # B, Hkv, G, D, N, W, C, mean, causal
     (1, 2, 4, 128, 2049, 32, 16, False, False), (1, 1, 8, 128, 5000, 64, 16, False, True),
     # chunk statistics laid where the scores will be: exactly full, one short, 20 chunks a head, odd N
     (1, 2, 4, 128, 1920, 32, 16, False, True), (1, 2, 4, 128, 1919, 32, 16, True, False),
-    (4, 8, 4, 128, 12345, 32, 16, False, True), (3, 3, 5, 64, 9001, 33, 7, True, True)]
+    (4, 8, 4, 128, 12345, 32, 16, False, True), (3, 3, 5, 64, 9001, 33, 7, True, True),
+    # one row group, few tokens: one chunk of 1152 keys, one key more; chunks of at least 256 keys
+    (65, 8, 1, 128, 1152, 8, 4, False, True), (65, 8, 1, 64, 1153, 8, 4, True, False), (1, 2, 2, 128, 511, 8, 4, False, True)]
 
 
 @pytest.mark.parametrize("case", CHUNK_CASES)
