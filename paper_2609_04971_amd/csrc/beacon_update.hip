@@ -36,6 +36,8 @@
 namespace bkv {
 namespace {
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
 // Query elements are loaded raw and widened only where they are used, so
 // that a prefetch is not waited on right after it is issued.
 __device__ __forceinline__ float widen(uint16_t v) { return dev::bf16_to_f32(v); }
@@ -77,7 +79,7 @@ __device__ __forceinline__ float cosine(float dot, float xn, float bn) {
 // arithmetic only where the two best cosines lie within a few 1e-7 of each
 // other.  bl [C][D + 4], xs [D] and the slots' squared norms bn2 in LDS.
 // QUAD (C <= 16): lanes 4c .. 4c+3 each take a quarter of slot c; else lane
-// c takes slot c.
+// c takes slot c, quarter by quarter (the sums are the same).
 template <int D, bool QUAD>
 __device__ __forceinline__ int nearest_slot(const float* bl, const float* xs, const float* bn2, float xn, int C,
                                             int lane) {
@@ -90,7 +92,27 @@ __device__ __forceinline__ int nearest_slot(const float* bl, const float* xs, co
         holds = c < C && part == 0;
         if (holds) key = ~dev::ord_key(cosine(dot, xn, bn2[c]));
     } else {
-        const float dot = (lane < C) ? row_dot<D>(&bl[lane * LD], xs) : 0.f;
+        float dot = 0.f;
+        if (lane < C) {
+            const f32x4* b = reinterpret_cast<const f32x4*>(&bl[lane * LD]);
+            const f32x4* x = reinterpret_cast<const f32x4*>(xs);
+            float part[4];
+#pragma unroll
+            for (int k = 0; k < 4; k += 2) {  // two quarters side by side: four would cost half the occupancy
+                f32x4 p[2];
+#pragma unroll
+                for (int i = 0; i < QD / 4; ++i)
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+                        const f32x4 u = b[(k + c) * (QD / 4) + i], v = x[(k + c) * (QD / 4) + i];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) p[c][e] = fmaf(u[e], v[e], i ? p[c][e] : 0.f);
+                    }
+#pragma unroll
+                for (int c = 0; c < 2; ++c) part[k + c] = (p[c][0] + p[c][1]) + (p[c][2] + p[c][3]);
+            }
+            dot = (part[0] + part[1]) + (part[2] + part[3]);
+        }
         holds = lane < C;
         if (holds) key = ~dev::ord_key(cosine(dot, xn, bn2[lane]));
     }
@@ -98,20 +120,49 @@ __device__ __forceinline__ int nearest_slot(const float* bl, const float* xs, co
     return (__ffsll(__ballot(holds && key == kmin)) - 1) >> (QUAD ? 2 : 0);
 }
 
-// Squared norm of a quarter of a row, summed over its four lanes.
+// Every squared norm is summed in one order, whoever forms it, so that equal
+// rows have equal norms and tie exactly: D / 64 neighbouring coordinates one
+// after the other, then their sums pairwise, as dev::wave_sum adds those of
+// 64 lanes.  sumsq_quarter is the part of one quarter (v(e) its coordinate
+// e), whose four results (a + b) + (c + d) makes the norm.
+template <int D, typename V>
+__device__ __forceinline__ float sumsq_quarter(V&& v) {
+    constexpr int PER = D / 64;
+    float s[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float l[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            l[j] = 0.f;
+#pragma unroll
+            for (int k = 0; k < PER; ++k) {
+                const float x = v((4 * i + j) * PER + k);
+                l[j] = fmaf(x, x, l[j]);
+            }
+        }
+        s[i] = (l[0] + l[1]) + (l[2] + l[3]);
+    }
+    return (s[0] + s[1]) + (s[2] + s[3]);
+}
+
+// (a + b) + (c + d) of the wave's four rows of 16 lanes, lane by lane.
+__device__ __forceinline__ float rows_sum(float v) {
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Squared norm of a row in LDS, a quarter of it to each of four lanes.
 template <int D>
 __device__ __forceinline__ float quarter_norm(const float* quarter, bool live) {
     float p = 0.f;
     if (live) {
-        const float4* r = reinterpret_cast<const float4*>(quarter);
+        f32x4 u[D / 16];
 #pragma unroll
-        for (int d4 = 0; d4 < D / 16; ++d4) {
-            const float4 u = r[d4];
-            p = fmaf(u.x, u.x, p);
-            p = fmaf(u.y, u.y, p);
-            p = fmaf(u.z, u.z, p);
-            p = fmaf(u.w, u.w, p);
-        }
+        for (int i = 0; i < D / 16; ++i) u[i] = reinterpret_cast<const f32x4*>(quarter)[i];
+        p = sumsq_quarter<D>([&](int e) { return u[e / 4][e % 4]; });
     }
     return dev::quad_sum(p);
 }
@@ -139,7 +190,7 @@ __global__ __launch_bounds__(64 * NW) void beacon_update_kernel(const T* __restr
                                                                 int Hq, int Hkv, int C) {
     constexpr int NT = 64 * NW;    // threads
     constexpr int LD = D + 4;      // padded row
-    constexpr int PER = D / 64;    // coordinates per lane in lane-parallel loops
+    constexpr int PER = D / 64;    // coordinates per lane in lane-parallel loops, neighbours
     constexpr int QD = D / 4;      // coordinates per lane of a slot's dot product (four lanes per slot)
     extern __shared__ __attribute__((aligned(16))) float smem[];
     float* bl = smem;                            // [C][LD]
@@ -170,7 +221,7 @@ __global__ __launch_bounds__(64 * NW) void beacon_update_kernel(const T* __restr
     // beacons of 16 slots, or of 64 with four waves, are one chunk).
     T xnext[PER];
 #pragma unroll
-    for (int k = 0; k < PER; ++k) xnext[k] = query_ptr(0)[lane + 64 * k];
+    for (int k = 0; k < PER; ++k) xnext[k] = query_ptr(0)[PER * lane + k];
     int cv = counts[(size_t)h * C + min(tid, C - 1)];
     asm volatile("" : "+v"(cv));
     const int n4 = C * D / 4;
@@ -204,13 +255,13 @@ __global__ __launch_bounds__(64 * NW) void beacon_update_kernel(const T* __restr
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
                 const float x = widen(xnext[k]);
-                xs[lane + 64 * k] = x;
+                xs[PER * lane + k] = x;
                 xn = fmaf(x, x, xn);
             }
             // the next query (the last one again at the end: no branch to
             // join, so nothing waits for it before its use)
 #pragma unroll
-            for (int k = 0; k < PER; ++k) xnext[k] = query_ptr(min(q + 1, nq - 1))[lane + 64 * k];
+            for (int k = 0; k < PER; ++k) xnext[k] = query_ptr(min(q + 1, nq - 1))[PER * lane + k];
             xn = dev::wave_sum(xn);
             wave_lds_fence();
             // lowest empty slot, if any
@@ -219,7 +270,7 @@ __global__ __launch_bounds__(64 * NW) void beacon_update_kernel(const T* __restr
             if (empty) {
                 chosen = __ffsll(empty) - 1;
 #pragma unroll
-                for (int k = 0; k < PER; ++k) bl[chosen * LD + lane + 64 * k] = xs[lane + 64 * k];
+                for (int k = 0; k < PER; ++k) bl[chosen * LD + PER * lane + k] = xs[PER * lane + k];
                 if (lane == 0) {
                     cnt[chosen] = 1;
                     bn2[chosen] = xn;
@@ -231,7 +282,7 @@ __global__ __launch_bounds__(64 * NW) void beacon_update_kernel(const T* __restr
                 float p = 0.f;
 #pragma unroll
                 for (int k = 0; k < PER; ++k) {
-                    const int d = lane + 64 * k;
+                    const int d = PER * lane + k;
                     const float bv = bl[chosen * LD + d];
                     const float nv = bv + (xs[d] - bv) * inv;
                     bl[chosen * LD + d] = nv;
@@ -273,18 +324,23 @@ __global__ __launch_bounds__(64 * NW) void beacon_update_kernel(const T* __restr
 // after which the waves apply the batch's updates to the beacons themselves,
 // query by query with the same arithmetic as above, and take the norms
 // afresh.  The numbers of a batch carry a few more roundings than direct
-// ones (a few 1e-7 of a cosine).  So a query whose two best cosines lie
-// within kNearTie is settled from the beacons themselves with the arithmetic
-// above (about one in 10^4), and where an update cancels most of a beacon
-// the batch ends, so that the next one starts from the beacons again: the
-// choices are those of the kernel above, and so are the results.
+// ones (a few 1e-7 of a cosine).  So where a query's two best cosines lie
+// within kNearTie (about one in 10^4) the chain ends before it, and the rest
+// of the batch is taken one by one with the arithmetic above; where an update
+// cancels most of a beacon the batch ends, so that the next one starts from
+// the beacons again: the choices are those of the kernel above, and so are
+// the results.  Equal beacons (repeated tokens) make ties of many queries:
+// with ties in every batch 128 heads of 2048 queries take 1858 us (64 slots;
+// the kernel above 2395) and 1572 (16 slots; 1587), 8 heads of 16 queries 12
+// (12); only many heads of a single batch lose by it (4608 of 16 slots 55
+// against 42, 1024 of 64 slots 130 against 91; without ties 38 against 44
+// and 76 against 94).
 //
 // Bound by the chain, about 100 instructions a query on one wave, and by the
-// batch's phases around it.  128 heads of 2048 queries: 64 slots 942 us
-// (2590 with the kernel above), 16 slots 990 (1761); 4608 heads of 256
+// batch's phases around it.  128 heads of 2048 queries: 64 slots 943 us
+// (2395 with the kernel above), 16 slots 996 (1584); 4608 heads of 256
 // queries, 64 slots: 860 (1850).
 constexpr int kBatchQ = 16;   // queries per batch: one MFMA tile
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 template <int D, int NW>
@@ -299,9 +355,10 @@ struct alignas(16) BatchLds {
         int slot;   // the slot a query joined; + kFill: it filled an empty one
         float inv;  // 1/n of the update
     } joined[kBatchQ];
-    float row[D], x0[D];                  // a beacon and the query of a choice settled directly
-    unsigned long long near;              // the slots it is between
-    int done;                             // queries of the batch that were taken; 0: settle the first directly
+    int done;                             // queries of the batch that the chain took
+    int alone;                            // the ones behind them to take one at a time
+    int cnt[64];                          // counts of the slots, for those
+    unsigned long long best[2][NW];       // each wave's nearest slot: inverted order key of the cosine, slot
     unsigned long long dirty;
 };
 constexpr int kFill = 256;
@@ -379,17 +436,51 @@ __global__ __launch_bounds__(64 * NW) void beacon_batch_kernel(const T* __restri
     for (int i = 0; i < Q / 4; ++i)
         beta[i] = slot < C ? reinterpret_cast<const f32x4*>(bh + (size_t)slot * D + g * Q)[i] : f32x4{0.f, 0.f, 0.f, 0.f};
     int cnt = (wave == 0 && lane < C) ? counts[(size_t)h * C + lane] : 1;  // wave 0: lane = slot
-    bool touched = false;          // wave 0: this lane's slot changed
-    unsigned long long dirty = 0;  // wave 0: the slots that did
+    bool touched = false;  // wave 0: this lane's slot changed
     auto store_norms = [&] {
-        float p = 0.f;
+        const float p = rows_sum(sumsq_quarter<D>([&](int e) { return beta[e / 4][e % 4]; }));
+        if (g == 0) sh.bn2[slot] = p;
+    };
+    // Query qq (coordinates at xq, squared norm xn) with the arithmetic of
+    // beacon_update_kernel, bit for bit.
+    auto take_one = [&](const float* xq, float xn, int qq, int odd) {
+        wave_lds_fence();  // the norms stored before
+        f32x4 x[Q / 4], p = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < Q / 4; ++i) x[i] = *reinterpret_cast<const f32x4*>(xq + g * L::QP + 4 * i);
 #pragma unroll
         for (int i = 0; i < Q / 4; ++i)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) p = fmaf(beta[i][e], beta[i][e], p);
-        p += dev::shfl_xor_f(p, 16);
-        p += dev::shfl_xor_f(p, 32);
-        if (g == 0) sh.bn2[slot] = p;
+            for (int e = 0; e < 4; ++e) p[e] = fmaf(beta[i][e], x[i][e], p[e]);
+        const float dot = rows_sum((p[0] + p[1]) + (p[2] + p[3]));
+        const bool holds = slot < C && g == 0;  // this lane speaks for its slot
+        const unsigned key = holds ? ~dev::ord_key(cosine(dot, xn, sh.bn2[slot])) : ~0u;
+        const unsigned kmin = dev::wave_min_u32(key);
+        int chosen = wave * 16 + ((__ffsll(__ballot(holds && key == kmin)) - 1) & 15);
+        if constexpr (NW > 1) {
+            if (lane == 0) sh.best[odd][wave] = ((unsigned long long)kmin << 32) | (unsigned)chosen;
+            __syncthreads();
+            unsigned long long b = sh.best[odd][0];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) b = min(b, sh.best[odd][w]);
+            chosen = (int)(unsigned)b;
+        }
+        chosen = __builtin_amdgcn_readfirstlane(chosen);
+        if (lane == chosen) {
+            ++cnt;
+            touched = true;
+        }
+        const float inv = 1.0f / (float)__builtin_amdgcn_readlane(cnt, chosen);
+        if (wave == chosen >> 4) {
+            if (slot == chosen) {
+#pragma unroll
+                for (int i = 0; i < Q / 4; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) beta[i][e] = beta[i][e] + (x[i][e] - beta[i][e]) * inv;
+            }
+            store_norms();
+        }
+        if (assign && tid == 0) assign[(size_t)h * nq + qq] = chosen;
     };
     store_norms();
     stage_queries(0);
@@ -438,7 +529,7 @@ __global__ __launch_bounds__(64 * NW) void beacon_batch_kernel(const T* __restri
         }
         __syncthreads();
         if (wave == 0) {  // the chain
-            int done = min(kBatchQ, nq - base);
+            int done = min(kBatchQ, nq - base), alone = 0;
             const unsigned long long empty = __ballot(lane < C && cnt == 0);
             if (empty) {
                 // while slots are empty each query fills the lowest one; the
@@ -454,6 +545,8 @@ __global__ __launch_bounds__(64 * NW) void beacon_batch_kernel(const T* __restri
                 // lanes past C never hold the largest product
                 const int ls = min(lane, C - 1);
                 const bool mine = lane < C;
+                const int all = done;
+                bool tie = false;
                 float d[kBatchQ];
 #pragma unroll
                 for (int q = 0; q < kBatchQ; ++q) d[q] = mine ? sh.dot[q][ls] : -INFINITY;
@@ -489,18 +582,14 @@ __global__ __launch_bounds__(64 * NW) void beacon_batch_kernel(const T* __restri
                     const int top = wave_max_i32(key);
                     const unsigned long long at = __ballot(key == top);
                     const int chosen = __ffsll(at) - 1;
-                    // another cosine within rounding of the largest: end the
-                    // batch before this query, or settle it if it is the first
-                    // (equal products of equal norms: the lowest, as ever)
+                    // another cosine within rounding of the largest: the chain
+                    // ends before this query
                     const int tb = top ^ ((top >> 31) & 0x7fffffff);
                     const unsigned long long near = __ballot(d[q] * rb >= __int_as_float(tb) - margin[q & 1]);
                     if (near & (near - 1)) {
-                        const float nb = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bn), chosen));
-                        if (xn != 0.f && near != __ballot(key == top && bn == nb)) {
-                            done = q;
-                            if (q == 0 && lane == 0) sh.near = near;
-                            return;
-                        }
+                        done = q;
+                        tie = true;
+                        return;
                     }
                     const float keep = 1.f - inv;
                     const float parts = fmaf(keep * keep, bn, inv * inv * xn);
@@ -519,63 +608,18 @@ __global__ __launch_bounds__(64 * NW) void beacon_batch_kernel(const T* __restri
                     rb = inv_root(bn);
                     inv = inv_count(cnt + 1);
                 });
+                if (tie) alone = all - done;
             }
-            dirty = __ballot(touched);
             if (lane >= done && lane < kBatchQ) sh.joined[lane] = {-1, 0.f};
+            sh.cnt[lane] = cnt;
             if (lane == 0) {
                 sh.done = done;
-                sh.dirty = dirty;
+                sh.alone = alone;
             }
         }
         __syncthreads();
         int done = __builtin_amdgcn_readfirstlane(sh.done);
-        if (done == 0) {
-            // the first query's choice is within rounding: it is settled
-            // between the slots that are, one after the other, as
-            // beacon_update_kernel forms their cosines, bit for bit, norms
-            // included (a changed slot's is summed over the wave, another's
-            // over four lanes)
-            for (int i = tid; i < D; i += NT) sh.x0[i] = sh.xs[buf][0][i / Q * L::QP + i % Q];
-            int chosen = 0;
-            unsigned best = ~0u;
-            for (unsigned long long m = sh.near; m; m &= m - 1) {
-                const int c = __ffsll(m) - 1;
-                if (slot == c) {
-#pragma unroll
-                    for (int i = 0; i < Q / 4; ++i) *reinterpret_cast<f32x4*>(&sh.row[g * Q + 4 * i]) = beta[i];
-                }
-                __syncthreads();
-                if (wave == 0) {
-                    auto sumsq = [&](const float* r) {
-                        float p = 0.f;
-#pragma unroll
-                        for (int k = 0; k < D / 64; ++k) p = fmaf(r[lane + 64 * k], r[lane + 64 * k], p);
-                        return dev::wave_sum(p);
-                    };
-                    const int part = (lane & 3) * Q;
-                    const float bn = ((dirty >> c) & 1ull) ? sumsq(sh.row) : quarter_norm<D>(&sh.row[part], true);
-                    const float dot = NW == 1 ? dev::quad_sum(row_dot<Q>(&sh.row[part], &sh.x0[part]))
-                                              : row_dot<D>(sh.row, sh.x0);
-                    const unsigned key = __builtin_amdgcn_readfirstlane(~dev::ord_key(cosine(dot, sumsq(sh.x0), bn)));
-                    if (key < best) {
-                        best = key;
-                        chosen = c;
-                    }
-                }
-                __syncthreads();
-            }
-            if (wave == 0) {
-                if (lane == chosen) {
-                    touched = true;
-                    ++cnt;
-                    sh.joined[0] = {lane, 1.0f / (float)cnt};
-                }
-                dirty = __ballot(touched);
-                if (lane == 0) sh.dirty = dirty;
-            }
-            __syncthreads();
-            done = 1;
-        }
+        const int alone = __builtin_amdgcn_readfirstlane(sh.alone);
         if (assign && tid < done) assign[(size_t)h * nq + base + tid] = sh.joined[tid].slot & (kFill - 1);
         // the batch's updates, every slot's in order (its queries all fill, or
         // all join)
@@ -600,12 +644,28 @@ __global__ __launch_bounds__(64 * NW) void beacon_batch_kernel(const T* __restri
             }
         }
         store_norms();
+        if (alone > 0) {
+            cnt = sh.cnt[lane];  // every wave follows the counts here
+            f32x4 x[Q / 4];
+#pragma unroll
+            for (int i = 0; i < Q / 4; ++i) x[i] = *reinterpret_cast<const f32x4*>(&sh.xs[buf][c16][g * L::QP + 4 * i]);
+            const float xn = rows_sum(sumsq_quarter<D>([&](int e) { return x[e / 4][e % 4]; }));  // of query c16
+            for (int i = 0; i < alone; ++i)
+                take_one(&sh.xs[buf][done + i][0],
+                         __int_as_float(__builtin_amdgcn_readlane(__float_as_int(xn), done + i)), base + done + i, i & 1);
+            done += alone;
+        }
         base += done;
         if (done < kBatchQ && base < nq) load_queries(base);
         stage_queries(buf ^ 1);
         buf ^= 1;
         __syncthreads();
     }
+    if (wave == 0) {
+        const unsigned long long m = __ballot(touched);
+        if (lane == 0) sh.dirty = m;
+    }
+    __syncthreads();
     const unsigned long long changed = sh.dirty;
     if (slot < C && ((changed >> slot) & 1ull)) {
 #pragma unroll
@@ -634,9 +694,10 @@ hipError_t launch_beacon_update(const bkv_dims& d, const void* q_new, int T, flo
     if (P == 0 || T == 0) return hipSuccess;
     const bool bf = d.dtype == BKV_BF16;
     // 16 queries or more per head (a batch), readable 16 bytes at a time: from
-    // there on the batches are ahead on every shape measured (16 queries:
-    // 8 heads of 16 slots 11 us against 17, 4608 heads of 16 slots 41 against
-    // 48, of 64 slots 76 against 135)
+    // there on the batches are ahead on every shape measured (16 queries: 8
+    // heads of 16 slots 7 us against 12, 4608 heads of 16 slots 38 against
+    // 44, 1024 heads of 64 slots 76 against 94; 8 queries would leave half of
+    // every batch empty)
     if ((long long)T * (d.Hq / d.Hkv) >= kBatchMin && (reinterpret_cast<uintptr_t>(q_new) & 15) == 0) {
         if (bf && d.D == 128)
             launch_batch<uint16_t, 128>(d, static_cast<const uint16_t*>(q_new), T, beacons, counts, assign, s);

@@ -204,3 +204,56 @@ def test_many_queries_at_an_unaligned_address():
     ref = _run_gpu(d, q, b, c)
     np.testing.assert_array_equal(host(b2).numpy(), ref[0])
     np.testing.assert_array_equal(host(c2).numpy(), ref[1])
+
+
+@pytest.mark.parametrize("dtype,D,C,G,T", [("bf16", 128, 12, 1, 40), ("bf16", 128, 64, 4, 9), ("fp32", 64, 24, 2, 16),
+                                           ("fp32", 128, 16, 4, 4)])
+def test_equal_beacons_tie_exactly(dtype, D, C, G, T):
+    # repeated tokens give equal queries and equal beacons: the lowest of the
+    # equal slots takes every one of them and stays as it is, however the
+    # queries come (one step per call, a prompt, a prompt read unaligned) and
+    # whether its norm was formed with the others' or after a join
+    d, q, b, c = _batch_inputs(dtype, D, 8, G, T, C, seed=C + D)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    low = torch.arange(16).view(2, 8) % (C // 2)
+    for i in range(2):
+        for h in range(8):
+            x = b[i, h, low[i, h]].to(tdt)
+            b[i, h, low[i, h]] = b[i, h, low[i, h] + C // 2] = b[i, h, C - 1] = x.float()
+            q[i, h * G:(h + 1) * G] = x
+    say(f"equal beacons {dtype} D={D} C={C} G={G} T={T}")
+    raw = torch.empty(q.numel() + 1, dtype=tdt, device="cuda")
+    odd = raw[1:].view(q.shape)
+    odd.copy_(q)
+    got = [_run_gpu(d, q, b, c), _run_gpu(d, odd, b, c)]
+    bs, cs, steps = b, c, []
+    for t in range(T):
+        bn, cn, a = _run_gpu(d, q[:, :, t:t + 1].contiguous(), bs, cs)
+        bs, cs = torch.from_numpy(bn), torch.from_numpy(cn)
+        steps.append(a)
+    got.append((bn, cn, np.concatenate(steps, axis=-1)))
+    c.view(16, C)[torch.arange(16), low.flatten()] += T * G
+    for bg, cg, a in got:
+        assert (a == low.numpy()[..., None]).all()
+        np.testing.assert_array_equal(cg, c.numpy())
+        np.testing.assert_array_equal(bg, b.numpy())
+
+
+def test_rounding_ties_of_different_beacons():
+    # coordinates of -1, 0 and 1: after a few joins products and norms of
+    # different beacons often agree to the last bit while their cosines, as
+    # one query at a time rounds them, do not
+    d, q, b, c = _batch_inputs("bf16", 64, 32, 7, 30, 48, seed=5)
+    g = torch.Generator().manual_seed(6)
+    q = torch.randint(-1, 2, q.shape, generator=g).to(q.dtype)
+    b, c = torch.randint(-1, 2, b.shape, generator=g).float(), torch.ones_like(c)
+    say("beacon batches of small integers")
+    got = _run_gpu(d, q, b, c)
+    bs, cs, steps = b, c, []
+    for t in range(q.shape[2]):
+        bn, cn, a = _run_gpu(d, q[:, :, t:t + 1].contiguous(), bs, cs)
+        bs, cs = torch.from_numpy(bn), torch.from_numpy(cn)
+        steps.append(a)
+    np.testing.assert_array_equal(got[2], np.concatenate(steps, axis=-1))
+    np.testing.assert_array_equal(got[1], cn)
+    np.testing.assert_array_equal(got[0], bn)
