@@ -329,7 +329,8 @@ __global__ __launch_bounds__(64 * NW) void beacon_update_kernel(const T* __restr
 // of the batch is taken one by one with the arithmetic above; where an update
 // cancels most of a beacon the batch ends, so that the next one starts from
 // the beacons again: the choices are those of the kernel above, and so are
-// the results.  Equal beacons (repeated tokens) make ties of many queries:
+// the results; batches with a norm or count out of the chain's reach (zero
+// queries among them) go one by one as well.  Equal beacons (repeated tokens) make ties of many queries:
 // with ties in every batch 128 heads of 2048 queries take 1858 us (64 slots;
 // the kernel above 2395) and 1572 (16 slots; 1587), 8 heads of 16 queries 12
 // (12); only many heads of a single batch lose by it (4608 of 16 slots 55
@@ -363,6 +364,8 @@ struct alignas(16) BatchLds {
 };
 constexpr int kFill = 256;
 constexpr float kNearTie = 4e-6f;  // cosines this close are settled by the arithmetic of one query at a time
+constexpr float kNormMin = 1e-18f, kNormMax = 1e18f;  // squared norms that the chain takes
+constexpr int kCountMax = (1 << 21) - kBatchQ;        // counts that it takes
 constexpr int kBatchMin = 16;  // queries per head from which the batches are taken
 
 // Maximum over the wave, the same in every lane.
@@ -551,9 +554,18 @@ __global__ __launch_bounds__(64 * NW) void beacon_batch_kernel(const T* __restri
 #pragma unroll
                 for (int q = 0; q < kBatchQ; ++q) d[q] = mine ? sh.dot[q][ls] : -INFINITY;
                 float bn = mine ? sh.bn2[ls] : 1.f;
+                // far from the ends of the float range only (a norm or a
+                // product under- or overflows at another place there), and
+                // with counts whose reciprocal below is exact; else one by one
+                const float xs2 = lane < all ? sh.gram[lane][lane] : 1.f;
+                if (__ballot((bn != 0.f && !(bn >= kNormMin && bn <= kNormMax)) ||
+                             !(xs2 >= kNormMin && xs2 <= kNormMax) || cnt >= kCountMax)) {
+                    done = 0;
+                    tie = true;
+                }
                 // 1/|b| (0 for a zero beacon), 1/n of the slot's next update
                 auto inv_root = [](float x) { return x == 0.f ? 0.f : __builtin_amdgcn_rsqf(x); };
-                auto inv_count = [](int n) {  // one Newton step past the 1-ulp reciprocal
+                auto inv_count = [](int n) {  // one Newton step past the 1-ulp reciprocal: 1/n to the last bit below 2.7 million
                     const float f = (float)n, r = __builtin_amdgcn_rcpf(f);
                     return fmaf(fmaf(-f, r, 1.f), r, r);
                 };
@@ -575,8 +587,7 @@ __global__ __launch_bounds__(64 * NW) void beacon_batch_kernel(const T* __restri
                     const f32x4* gq = gr[q & 1];
                     const float xn = gq[q / 4][q % 4];
                     // the cosines but for the common factor 1/|x|, which moves
-                    // no argmax (a zero query has all its products 0), as
-                    // integers of the same order (-0 as +0)
+                    // no argmax, as integers of the same order (-0 as +0)
                     int key = __float_as_int(fmaf(d[q], rb, 0.f));
                     key ^= (key >> 31) & 0x7fffffff;
                     const int top = wave_max_i32(key);

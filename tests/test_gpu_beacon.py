@@ -257,3 +257,39 @@ def test_rounding_ties_of_different_beacons():
     np.testing.assert_array_equal(got[2], np.concatenate(steps, axis=-1))
     np.testing.assert_array_equal(got[1], cn)
     np.testing.assert_array_equal(got[0], bn)
+
+
+@pytest.mark.parametrize("scale", [0.0, 1e-25, 1e-23, 3e-20, 1e-19, 1e-17, 1e17, 1e19, 2e19])
+@pytest.mark.parametrize("C", [16, 24])
+def test_batches_at_the_ends_of_the_range(scale, C):
+    # squared norms that are 0 or infinite in fp32, or nearly: cosines are then
+    # 0 (slot 0 takes the query) or whatever one query at a time makes of them
+    d, q, b, c = _batch_inputs("fp32", 128, 2, 2, 16, C, seed=C)
+    q[:, :, 4:9] *= scale
+    b[:, 0, 3] *= scale
+    say(f"beacon batches, some queries and a beacon times {scale}, C={C}")
+    got = _run_gpu(d, q, b, c)
+    bs, cs, steps = b, c, []
+    for t in range(q.shape[2]):
+        bn, cn, a = _run_gpu(d, q[:, :, t:t + 1].contiguous(), bs, cs)
+        bs, cs = torch.from_numpy(bn), torch.from_numpy(cn)
+        steps.append(a)
+    np.testing.assert_array_equal(got[2], np.concatenate(steps, axis=-1))
+    np.testing.assert_array_equal(got[1], cn)
+    np.testing.assert_array_equal(got[0], bn)
+    if scale < 1e-23:  # all cosines of these queries are 0
+        assert (got[2].reshape(2, 2, 16, 2)[:, :, 4:9] == 0).all()
+
+
+def test_batches_assign_real_slots_whatever_the_inputs():
+    # not a number, of either sign, in every product: still a slot below C,
+    # and the counts still sum to the queries seen
+    for bits in (0x7fc00000, 0xffc00000, 0x7fffffff, 0xffffffff, 0x7f800000, 0xff800000):
+        bad = torch.from_numpy(np.array([bits], np.uint32).view(np.float32))
+        d, q, b, c = _batch_inputs("fp32", 64, 2, 4, 8, 5, seed=2)
+        q[:, :, 3] = bad
+        b[:, 1] = bad
+        say(f"beacon batches with {bits:#x}")
+        _, cg, a = _run_gpu(d, q, b, c)
+        assert ((a >= 0) & (a < 5)).all()
+        assert int(cg.sum()) == int(c.sum()) + q.shape[0] * q.shape[1] * q.shape[2]
