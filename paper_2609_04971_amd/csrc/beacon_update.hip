@@ -338,8 +338,8 @@ __global__ __launch_bounds__(64 * NW) void beacon_update_kernel(const T* __restr
 // and 76 against 94).
 //
 // Bound by the chain, about 100 instructions a query on one wave, and by the
-// batch's phases around it.  128 heads of 2048 queries: 64 slots 943 us
-// (2395 with the kernel above), 16 slots 996 (1584); 4608 heads of 256
+// batch's phases around it.  128 heads of 2048 queries: 64 slots 948 us
+// (2395 with the kernel above), 16 slots 1019 (1584); 4608 heads of 256
 // queries, 64 slots: 860 (1850).
 constexpr int kBatchQ = 16;   // queries per batch: one MFMA tile
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
@@ -356,7 +356,7 @@ struct alignas(16) BatchLds {
         int slot;   // the slot a query joined; + kFill: it filled an empty one
         float inv;  // 1/n of the update
     } joined[kBatchQ];
-    int done;                             // queries of the batch that the chain took
+    int done;                             // queries of the batch that the chain took; + kFill: empty slots are left
     int alone;                            // the ones behind them to take one at a time
     int cnt[64];                          // counts of the slots, for those
     unsigned long long best[2][NW];       // each wave's nearest slot: inverted order key of the cosine, slot
@@ -487,13 +487,19 @@ __global__ __launch_bounds__(64 * NW) void beacon_batch_kernel(const T* __restri
     };
     store_norms();
     stage_queries(0);
+    if (wave == 0) {
+        const bool left = __ballot(lane < C && cnt == 0) != 0;
+        if (lane == 0) sh.done = left ? kFill : 0;
+    }
     __syncthreads();
 
     int buf = 0;
+    bool filling = (__builtin_amdgcn_readfirstlane(sh.done) & kFill) != 0;
     for (int base = 0; base < nq;) {
         load_queries(base + kBatchQ);  // the next batch, unless this one ends early
         // dot products with the wave's slots; wave 0: with each other too
-        {
+        // (queries that fill empty slots need neither)
+        if (!filling) {
             f32x4 x[Q / 4];
 #pragma unroll
             for (int i = 0; i < Q / 4; ++i) x[i] = *reinterpret_cast<const f32x4*>(&sh.xs[buf][c16][g * L::QP + 4 * i]);
@@ -533,10 +539,10 @@ __global__ __launch_bounds__(64 * NW) void beacon_batch_kernel(const T* __restri
         __syncthreads();
         if (wave == 0) {  // the chain
             int done = min(kBatchQ, nq - base), alone = 0;
-            const unsigned long long empty = __ballot(lane < C && cnt == 0);
-            if (empty) {
+            if (filling) {
                 // while slots are empty each query fills the lowest one; the
                 // batch ends with the last
+                const unsigned long long empty = __ballot(lane < C && cnt == 0);
                 done = min(done, (int)__popcll(empty));
                 const int q = __popcll(empty & ((1ull << lane) - 1));
                 if (((empty >> lane) & 1ull) && q < done) {
@@ -623,13 +629,16 @@ __global__ __launch_bounds__(64 * NW) void beacon_batch_kernel(const T* __restri
             }
             if (lane >= done && lane < kBatchQ) sh.joined[lane] = {-1, 0.f};
             sh.cnt[lane] = cnt;
+            const bool left = __ballot(lane < C && cnt == 0) != 0;
             if (lane == 0) {
-                sh.done = done;
+                sh.done = done | (left ? kFill : 0);
                 sh.alone = alone;
             }
         }
         __syncthreads();
         int done = __builtin_amdgcn_readfirstlane(sh.done);
+        filling = (done & kFill) != 0;
+        done &= kFill - 1;
         const int alone = __builtin_amdgcn_readfirstlane(sh.alone);
         if (assign && tid < done) assign[(size_t)h * nq + base + tid] = sh.joined[tid].slot & (kFill - 1);
         // the batch's updates, every slot's in order (its queries all fill, or
