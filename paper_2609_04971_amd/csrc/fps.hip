@@ -489,6 +489,8 @@ constexpr int kLazyMaxPicks = 128;          // t_j is a byte and the picked rows
 constexpr size_t kLazyMaxLds = 160 * 1024 - 1024;
 constexpr unsigned kPicked = 0xffffffffu;   // above the key of every value
 
+constexpr unsigned kHighest = kPicked - 1;  // the highest key a row that is not picked may have: one NaN's own is kPicked
+
 // Sum over the LPR lanes of a row, the same in each of them.
 template <int LPR>
 __device__ __forceinline__ float row_lanes_sum(float v) {
@@ -632,7 +634,7 @@ __global__ __launch_bounds__(kLazyThreads, 4) void fps_lazy_kernel(const T* src,
                 p = row_lanes_sum<LPR>(p);
                 const int j = jb + u * RPI + sub;
                 if (c == 0 && j < j1 && !(mark && key[j] == kPicked)) {
-                    key[j] = dev::ord_key(p * inv[j] * scale);
+                    key[j] = min(dev::ord_key(p * inv[j] * scale), kHighest);
                     seen[j] = mark;
                 }
             }
@@ -742,7 +744,7 @@ __global__ __launch_bounds__(kLazyThreads, 4) void fps_lazy_kernel(const T* src,
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
                     if (c16 == v && 16 * b2 + 4 * g + v < cnt) {
-                        const unsigned kk = ~low_key[b2][v];
+                        const unsigned kk = min(~low_key[b2][v], kHighest);
                         key[jo[b2][v]] = kk;
                         seen[jo[b2][v]] = (unsigned char)k;
                         atomicMin(low, ((unsigned long long)kk << 32) | (unsigned)jo[b2][v]);

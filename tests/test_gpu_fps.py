@@ -194,6 +194,21 @@ def test_fps_lazy_repeated_axes():
     assert host(bkv.fps(x, 40))[0].tolist() == [0, 2, 1, 3] + list(range(4, 40))
 
 
+@pytest.mark.parametrize("where", ["one", "all"])
+@pytest.mark.parametrize("bits", [0x7fffffff, 0xffffffff, 0x7fc00000, 0xffc00000, 0x7f800000])
+def test_fps_lazy_picks_are_distinct_whatever_the_inputs(bits, where):
+    # inputs that are not finite leave the ranking open, but not that every
+    # pick is another row of the set
+    q = queries(2, 1100, 64, "fp32", seed=1)
+    bad = torch.from_numpy(np.array([bits], np.uint32).view(np.float32)).cuda()
+    if where == "all":
+        q[:] = bad
+    else:
+        q[:, :, 500] = bad
+    for p in host(bkv.fps(q, 40)).reshape(2, 40).tolist():
+        assert len(set(p)) == 40 and 0 <= min(p) and max(p) < 1100
+
+
 def test_fps_lazy_largest_set_greedy_rule():
     q = queries(2, 16384, 128, "bf16", seed=16384)
     picks = bkv.fps(q, 16)
