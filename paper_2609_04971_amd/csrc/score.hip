@@ -721,61 +721,65 @@ __device__ __forceinline__ void wait_vmem() {
 // 16 bytes lane l presents to the MFMA, i.e. chunk 4 v + l / 16 of row
 // 16 rt + l % 16; plus the head's occupied-slot list.
 //
-// One wave per row tile, four tiles per workgroup, and every lane forms its
-// vectors from the inputs by itself: a chain of two memory round trips (the
-// slots' counts, then the row).  Bound by those two trips on small layers
-// and by the rows' bytes on large ones.  Staging up to 144 rows through LDS
-// in one workgroup per head, with the slot list walked by one thread, took
-// 9 to 30 us per layer and 99 us for 4608 heads of 144 rows (170 MB written).
-constexpr int kRowTilesPerBlock = kWaves;
-
+// A wave takes two vectors of a row tile, v and v + NV / 2, whose coordinates
+// RoPE turns together (D = 128: two waves per tile; D = 64: one).  Every lane
+// forms its 16 bytes of each from the inputs by itself: a chain of two memory
+// round trips (the slots' counts, then the row), with no barrier, since every
+// wave lists the slots for itself.  Bound by those trips and the fetch of the
+// code on small layers, by the rows' bytes on large ones.  us, beside rows
+// staged through LDS by one workgroup per head, and a whole tile per wave
+// with each half of a pair formed apart:
+//   heads x rows (D = 128)   1 x 16   16 x 72   32 x 544   1024 x 144   4608 x 144   4608 x 40
+//   this kernel               3.0      4.0       7.1        14.4         68.5         27.6
+//   through LDS               3.0      5.3      19.2        14.9         84.7         31.1
+//   a tile per wave           5.1      6.2       9.0        17.2         71.1         35.5
 template <int D>
 __global__ __launch_bounds__(kThreads) void rows_kernel(Args a) {
-    constexpr int NV = Op<uint16_t, D>::NV, H = D / 2;
-    __shared__ int act[kMaxC];
-    __shared__ int nact_s;
-    const int h = blockIdx.x, lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
+    constexpr int NV = Op<uint16_t, D>::NV, H = D / 2, WPT = NV / 2;  // waves per tile
+    __shared__ int act_s[kWaves][kMaxC];
+    const int h = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, c16 = lane & 15;
+    int* act = act_s[wave];
+    const bool occupied = lane < a.C && a.counts[(size_t)h * a.C + lane] > 0;  // C <= 64
     if (blockIdx.y == 0) reset_head_control(a, h);
-    active_slots(a, h, act, &nact_s);
-    const int nact = nact_s, R = nact + a.G * a.W;
-    if (blockIdx.y == 0) {
+    const unsigned long long m = __ballot(occupied);
+    const int nact = __popcll(m), R = nact + a.G * a.W;
+    if (occupied) act[__popcll(m & ((1ull << lane) - 1))] = lane;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // a wave's LDS accesses execute in order
+    if (blockIdx.y == 0 && wave == 0) {
         int* meta = a.rmeta + (size_t)h * kMetaWords;
-        if (threadIdx.x == 0) meta[0] = nact;
-        for (int c = threadIdx.x; c < nact; c += kThreads) meta[kMetaAct + c] = act[c];
+        if (lane == 0) meta[0] = nact;
+        if (lane < nact) meta[kMetaAct + lane] = act[lane];
     }
-    const int rt = blockIdx.y * kRowTilesPerBlock + (threadIdx.x >> 6);
+    const int rt = (blockIdx.y * kWaves + wave) / WPT, v = wave % WPT;
     if (rt * 16 >= a.R_pad_max) return;
-    const int r = rt * 16 + c16;
-    dev::u32x4 val[NV];
+    const int r = rt * 16 + c16, i0 = 8 * (4 * v + g);
+    dev::u32x4 lo = {0u, 0u, 0u, 0u}, hi = lo;  // elements i0 .. i0 + 7 and those H further
     if (r < nact) {  // an occupied beacon, rotated to the step and rounded
         const float* beta = a.beacons + ((size_t)h * a.C + act[r]) * D;
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            const int e0 = 8 * (4 * v + g), i0 = e0 & (H - 1);  // elements e0 .. e0 + 7, pairs i0 .. i0 + 7
+        for (int e = 0; e < 8; e += 2) {
+            uint16_t x[2], y[2];
 #pragma unroll
-            for (int e = 0; e < 8; e += 2) {
-                uint16_t o[2];
-#pragma unroll
-                for (int k = 0; k < 2; ++k) {
-                    const int i = i0 + e + k;
-                    float2 p = make_float2(beta[i], beta[i + H]);
-                    if (a.rope_cos) p = rope_pair(p.x, p.y, a.rope_cos[i], a.rope_sin[i]);
-                    o[k] = dev::f32_to_bf16_rne(e0 < H ? p.x : p.y);
-                }
-                val[v][e / 2] = (unsigned)o[0] | ((unsigned)o[1] << 16);
+            for (int k = 0; k < 2; ++k) {
+                const int i = i0 + e + k;
+                float2 p = make_float2(beta[i], beta[i + H]);
+                if (a.rope_cos) p = rope_pair(p.x, p.y, a.rope_cos[i], a.rope_sin[i]);
+                x[k] = dev::f32_to_bf16_rne(p.x);
+                y[k] = dev::f32_to_bf16_rne(p.y);
             }
+            lo[e / 2] = (unsigned)x[0] | ((unsigned)x[1] << 16);
+            hi[e / 2] = (unsigned)y[0] | ((unsigned)y[1] << 16);
         }
-    } else {  // a recent query of the group, or padding
+    } else if (r < R) {  // a recent query of the group (else padding)
         const int b = h / a.Hkv, kh = h % a.Hkv;
         const uint16_t* q = reinterpret_cast<const uint16_t*>(a.qwin) +
-                            (((size_t)b * a.Hq + (size_t)kh * a.G) * a.W + (r - nact)) * D;
-#pragma unroll
-        for (int v = 0; v < NV; ++v)
-            val[v] = r < R ? *reinterpret_cast<const dev::u32x4*>(q + 8 * (4 * v + g)) : dev::u32x4{0u, 0u, 0u, 0u};
+                            (((size_t)b * a.Hq + (size_t)kh * a.G) * a.W + (r - nact)) * D + i0;
+        lo = *reinterpret_cast<const dev::u32x4*>(q);
+        hi = *reinterpret_cast<const dev::u32x4*>(q + H);
     }
     dev::u32x4* out = reinterpret_cast<dev::u32x4*>(a.rows) + ((size_t)h * a.R_pad_max + rt * 16) * D / 8 + lane;
-#pragma unroll
-    for (int v = 0; v < NV; ++v) out[v * 64] = val[v];
+    out[v * 64] = lo;
+    out[(v + NV / 2) * 64] = hi;
 }
 
 // Row group rg (rows 16 RT rg .. 16 RT (rg + 1) - 1) of head h into registers.
@@ -1733,8 +1737,8 @@ __global__ __launch_bounds__(kThreads, 2) void evict_kernel(Args a) {
 
 template <int D, int RT>
 hipError_t launch_fast_rt(const Args& a, hipStream_t s) {
-    const int row_blocks = (a.R_pad_max / 16 + kRowTilesPerBlock - 1) / kRowTilesPerBlock;
-    hipLaunchKernelGGL((rows_kernel<D>), dim3(a.P, row_blocks), dim3(kThreads), 0, s, a);
+    const int row_waves = a.R_pad_max / 16 * (Op<uint16_t, D>::NV / 2);
+    hipLaunchKernelGGL((rows_kernel<D>), dim3(a.P, (row_waves + kWaves - 1) / kWaves), dim3(kThreads), 0, s, a);
     const bool multi = a.R_pad_max > RT * 16;
     // four row groups of 7 to 9 tiles (R of about 400 to 576): one per wave
     if constexpr (RT >= 7) {

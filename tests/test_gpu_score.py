@@ -244,3 +244,30 @@ def test_score_key_chunks(case):
     assert_scores_close(host(scores).numpy()[sel], s_ref[sel])
     assert_scores_close(host(lse).numpy()[sel], lse_ref[sel], "row_lse")
     assert not torch.isnan(scores).any()
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("C,occupied,G,Wn", [(64, 0.5, 1, 1), (64, 1.0, 1, 0), (33, 0.9, 3, 5), (16, 0.0, 2, 40), (0, 1.0, 7, 64)])
+def test_score_observation_rows(D, C, occupied, G, Wn):
+    # row tiles of beacons only, of both kinds and of queries only; empty
+    # slots between occupied ones; heads with as few as one row
+    import paper_2609_04971_amd as bkv
+    w = W("rows", B=3, Hq=2 * G, Hkv=2, D=D, N=700, W=Wn, C=C, budget=64, revisit_frac=0.1)
+    x = synth.make_layer(w, seed=C + D, N_cap=700)
+    if C:
+        g = torch.Generator().manual_seed(C)
+        x["counts"] = x["counts"] * (torch.rand(x["counts"].shape, generator=g) < occupied).int()
+        x["counts"][0, 0] = 0
+        x["counts"][0, 1] = torch.arange(C) == C - 1  # the last slot alone
+    d = dims_of(w)
+    ws = bkv.workspace(d, bkv.OP_SCORE)
+    scores = torch.empty(3, 2, 700, device="cuda")
+    lse = torch.empty(3, 2, C + G * Wn, device="cuda")
+    xd = to_dev(x)
+    bkv.score(d, xd["K"], xd["q_win"], xd["beacons"], xd["counts"], scores, ws, row_lse=lse, rope_cos=xd["rope_cos"],
+              rope_sin=xd["rope_sin"])
+    assert bkv.device_status(ws) == bkv.OK
+    s_ref, lse_ref = oracle.score(x["K"], x["q_win"], x["beacons"], x["counts"], N=700, rope_cos=x["rope_cos"],
+                                  rope_sin=x["rope_sin"])
+    assert_scores_close(host(scores).numpy(), s_ref)
+    assert_scores_close(host(lse).numpy(), lse_ref, "row_lse")
