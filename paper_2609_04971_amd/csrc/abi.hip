@@ -34,7 +34,14 @@ __global__ void ws_init_kernel(int* ws, int nwords, int P, int budget) {
 
 }  // namespace
 
-WsLayout ws_layout(const bkv_dims& d) {
+// Cost of chunks of kc keys: the rounds that their work items take over the
+// machine, times their length (see kChunkTail).
+static float chunk_cost(const bkv_dims& d, int P, int kc) {
+    const float rounds = 2.f * (float)P * (float)((d.N + kc - 1) / kc) / kScoreSlots + kChunkTail;
+    return (rounds > kChunkRounds ? rounds : kChunkRounds) * (float)((kc < d.N ? kc : d.N) + kChunkFixed);
+}
+
+WsLayout ws_layout(const bkv_dims& d, int flags) {
     WsLayout L;
     memset(&L, 0, sizeof L);
     const int P = d.B * d.Hkv;
@@ -92,7 +99,23 @@ WsLayout ws_layout(const bkv_dims& d) {
         const bool few = (long long)P * d.N < kFewTokens;
         const int longest = multi ? kMultiKeyChunk : few ? kFewKeyChunk : kOneGroupKeyChunk;
         const int n = min(room, max(max(1, items / P), (d.N + longest - 1) / longest));
-        L.key_chunk = max(kShortKeyChunk, ((d.N + n - 1) / n + kKeyChunkUnit - 1) / kKeyChunkUnit * kKeyChunkUnit);
+        auto even = [&](int n) {  // n even chunks
+            return max(kShortKeyChunk, ((d.N + n - 1) / n + kKeyChunkUnit - 1) / kKeyChunkUnit * kKeyChunkUnit);
+        };
+        L.key_chunk = even(n);
+        // shorter chunks where that saves a nearly empty round (kChunkTail)
+        const bool mean = (flags & BKV_SCORE_MEAN) != 0;
+        float best = chunk_cost(d, P, L.key_chunk);
+        if (!mean && L.rtg > kFewTiles) best *= kChunkMargin;
+        for (int want = 1024; want >= 768 && (mean || !multi); want -= kKeyChunkUnit) {
+            const int m = (d.N + want - 1) / want, kc = even(m);
+            if (m > room || kc != want || (!mean && L.rtg > kFewTiles && want < 1024)) continue;
+            const float c = chunk_cost(d, P, kc);
+            if (c < best) {
+                best = c;
+                L.key_chunk = kc;
+            }
+        }
         L.nch = (d.N + L.key_chunk - 1) / L.key_chunk;
     }
     L.lse2 = off;
@@ -218,7 +241,7 @@ bkv_status bkv_score_ex(const bkv_dims* d, int32_t flags, const void* K, const v
     st = check_score_args(d, K, q_win, beacons, counts, rope_cos, rope_sin, scale);
     if (st != BKV_OK) return st;
     if (!scores) return BKV_ERR_INVALID;
-    const WsLayout L = ws_layout(*d);
+    const WsLayout L = ws_layout(*d, flags);
     if (!ws || ws_bytes < L.score_end || !aligned16(ws)) return BKV_ERR_WORKSPACE;
     return map_hip(launch_score(*d, L, flags, K, q_win, beacons, counts, rope_cos, rope_sin, scale, scores, row_lse, ws,
                                 stream));
@@ -303,7 +326,7 @@ bkv_status evict_check(const bkv_dims* d, int32_t flags, const void* K, const vo
 bkv_status evict_enqueue(const bkv_dims* d, int32_t flags, void* K, void* V, const void* q_win, const float* beacons,
                          const int32_t* counts, const float* rope_cos, const float* rope_sin, float scale,
                          int32_t* kept, float* scores, float* row_lse, void* ws, hipStream_t stream) {
-    const WsLayout L = ws_layout(*d);
+    const WsLayout L = ws_layout(*d, flags);
     char* w = static_cast<char*>(ws);
     float* sc = scores ? scores : reinterpret_cast<float*>(w + L.scores);
     int32_t* kp = kept ? kept : reinterpret_cast<int32_t*>(w + L.kept);

@@ -119,6 +119,29 @@ constexpr int kFastTiles = 9;
 // which is chunks of at most 1152 keys, and kMultiScoreItems of them in all
 // unless there are so many heads that the count a head gets would be a
 // coarse one (128 x 4096: 4 chunks 127, 5 145, 6 143).
+//
+// The chunk's cost: these limits look at the length of a chunk, not at how
+// full the last round of items is, which cost up to 13 % against 1024-key
+// chunks (256 with fewer than 512 such) where a round was nearly empty, most
+// of all in the mean form, whose items are longer, and in heads of few rows.
+// There chunks of 1024, 896 and 768 keys are taken where rounds times length
+// is less,
+//     max(2 P nch / kScoreSlots + kChunkTail, kChunkRounds) (keys + kChunkFixed),
+// fitted over 2500 measured shapes.  In the max form several row groups keep
+// the limits above (5 of 900 shapes lose more than 1 % by them), and one group
+// of more than kFewTiles tiles takes 1024 keys only, and only 2 % below.
+// us, chunk by the limits -> by the cost (beside 1024 or 256 keys):
+//   92 x 5282, 176 rows, mean   1152 120 -> 768 89 (113)
+//   280 x 4148, 520 rows, mean  1152 438 -> 896 393 (405)
+//   94 x 5248, 144 rows, mean   1152 85 -> 768 77 (83)
+//   152 x 3413, 72 rows, mean   1152 51.6 -> 896 46.0 (45.6)
+//   58 x 7522, 8 rows           1024 36.1 -> 768 31.3 (32.8)
+//   12 x 46437, 48 rows         1152 58.6 -> 896 52.2 (56.3)
+// The losses are smaller: 28 x 29678, 656 rows, mean 505 -> 527 (544).
+// Over 900 other shapes 32 are more than 1 % behind 1024 or 256 keys, 5 more
+// than 4 % (19 and 47 of 500, counted alike, before); 15 % ahead on average.
+constexpr float kChunkTail = 0.25f, kChunkRounds = 2.5f, kChunkMargin = 0.98f;
+constexpr int kChunkFixed = 150, kFewTiles = 5;
 constexpr int kOneGroupKeyChunk = 1664;
 constexpr int kFewKeyChunk = 1152;    // one row group, fewer than kFewTokens tokens in all
 constexpr long long kFewTokens = 1750000;
@@ -137,7 +160,9 @@ constexpr int kTkMaxHeads = 64;
 constexpr int kTkMinN = 8192;
 constexpr int kFastRowGroups = 8;
 
-WsLayout ws_layout(const bkv_dims& d);
+// flags (BKV_SCORE_*) choose the score's key chunks only; every offset and
+// size is the same for all of them.
+WsLayout ws_layout(const bkv_dims& d, int flags = 0);
 
 // ---- the whole eviction (bkv_evict_ex), split so that a caller can check the
 // arguments before it enqueues anything of its own -----------------------------

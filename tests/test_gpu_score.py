@@ -4,6 +4,7 @@ import pytest
 import torch
 
 import oracle
+from score_layout import CHUNK_CASES, chunk_dims
 from gpu_util import assert_scores_close, dims_of, host, say, to_dev
 from paper_2609_04971_amd import synth
 
@@ -204,31 +205,16 @@ def test_score_key_far_above_its_lanes_first_keys(mean):
     say(f"  max |diff| {err:.2e}")
 
 
-# Key chunks: the longest of one and of several row groups (1664 and 1152
-# keys) and one key more, chunks that end inside a wave's 32-key group or
-# leave waves without keys, and few heads (the shortest chunks).
-CHUNK_CASES = [  # B, Hkv, G, D, N, W, C, mean, causal
-    (33, 16, 1, 128, 1664, 8, 4, False, True), (33, 16, 1, 128, 1665, 8, 4, True, False), (33, 16, 1, 64, 1537, 16, 0, False, False),
-    (65, 8, 1, 128, 127, 4, 3, False, True), (65, 8, 1, 64, 33, 4, 3, True, True), (16, 8, 4, 128, 4223, 32, 16, False, False),
-    (33, 8, 7, 128, 1152, 64, 16, False, True), (33, 8, 7, 64, 1153, 64, 16, True, False), (33, 8, 5, 128, 1151, 40, 8, True, True),
-    (1, 2, 4, 128, 2049, 32, 16, False, False), (1, 1, 8, 128, 5000, 64, 16, False, True),
-    # chunk statistics laid where the scores will be: exactly full, one short, 20 chunks a head, odd N
-    (1, 2, 4, 128, 1920, 32, 16, False, True), (1, 2, 4, 128, 1919, 32, 16, True, False),
-    (4, 8, 4, 128, 12345, 32, 16, False, True), (3, 3, 5, 64, 9001, 33, 7, True, True),
-    # one row group, few tokens: one chunk of 1152 keys, one key more; chunks of at least 256 keys
-    (65, 8, 1, 128, 1152, 8, 4, False, True), (65, 8, 1, 64, 1153, 8, 4, True, False), (1, 2, 2, 128, 511, 8, 4, False, True)]
-
-
 @pytest.mark.parametrize("case", CHUNK_CASES)
 def test_score_key_chunks(case):
     import paper_2609_04971_amd as bkv
-    B, Hkv, G, D, N, Wn, C, mean, causal = case
+    B, Hkv, G, D, N, Wn, C, mean, causal = case[:9]
+    d = chunk_dims(case, N_cap=N + 3)
     w = W("chunk", B=B, Hq=Hkv * G, Hkv=Hkv, D=D, N=N, W=Wn, C=C, budget=64, revisit_frac=0.1)
-    x = synth.make_layer(w, seed=N + D, N_cap=N + 3)
+    x = {k: host(v) for k, v in synth.make_layer(w, seed=N + D, N_cap=N + 3, device="cuda").items()}
     if C > 2:
         x["counts"][:, :, 1] = 0  # empty slots: the occupied ones are listed past them
     x["K"][:, :, N:] = float("nan")  # rows past N are never scored
-    d = dims_of(w, N_cap=N + 3)
     ws = bkv.workspace(d, bkv.OP_SCORE)
     scores = torch.full((B, Hkv, N), float("nan"), device="cuda")
     lse = torch.full((B, Hkv, C + G * Wn), float("nan"), device="cuda")

@@ -1,0 +1,31 @@
+"""How score calls are split into key chunks (host only, nothing is launched)."""
+import pytest
+
+from score_layout import CHUNK_CASES, chunk_dims, layout
+import paper_2609_04971_amd as bkv
+
+
+@pytest.mark.parametrize("case", CHUNK_CASES, ids=lambda c: "-".join(map(str, c[:7])))
+def test_chunk_cases_are_what_they_are_meant_to_be(case):
+    L = layout(chunk_dims(case), mean=case[7])
+    assert (L.groups, L.key_chunk, L.nch, L.in_scores) == case[9:]
+
+
+def test_chunks_cover_the_head_and_their_statistics_fit():
+    # every form of the rule, over sizes, rows and head counts: the chunks cover
+    # the head, none is empty, none longer than the kernels' LDS holds, and the
+    # statistics fit the workspace or, per head, the room of its scores
+    for P in (1, 2, 7, 36, 61, 64, 65, 200, 513, 5000):
+        for N in (1, 33, 255, 256, 257, 1151, 1153, 1665, 4224, 6657, 16384, 29999, 65536):
+            if P * N > 1 << 25:
+                continue
+            for R in (1, 16, 40, 80, 96, 144, 145, 192, 288, 384, 464, 576, 1024):
+                for mean in (False, True):
+                    d = bkv.dims(B=P, Hq=1, Hkv=1, D=128, N=N, W=R, C=0, budget=R, dtype="bf16")
+                    L = layout(d, mean)
+                    at = (P, N, R, mean, L.key_chunk, L.nch)
+                    assert L.key_chunk % 128 == 0 and 0 <= L.nch * L.key_chunk - N < L.key_chunk, at
+                    assert L.key_chunk <= (1664 if L.groups == 1 else 1152), at
+                    assert L.nch <= L.nch_ws or 2 * L.nch * L.R_pad_max <= N, at
+                    other = layout(d, not mean)  # one workspace serves both forms
+                    assert (L.evict_end, L.part_z, L.lse2) == (other.evict_end, other.part_z, other.lse2), at
