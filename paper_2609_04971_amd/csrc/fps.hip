@@ -487,9 +487,8 @@ constexpr int kLazyThreads = 512;
 constexpr int kLazyWaves = kLazyThreads / 64;
 constexpr int kLazyMaxPicks = 128;          // t_j is a byte and the picked rows stay in LDS
 constexpr size_t kLazyMaxLds = 160 * 1024 - 1024;
-constexpr unsigned kPicked = 0xffffffffu;   // above the key of every value
+constexpr unsigned kPicked = 0xffffffffu;   // above the key of every value but one NaN
 
-constexpr unsigned kHighest = kPicked - 1;  // the highest key a row that is not picked may have: one NaN's own is kPicked
 
 // Sum over the LPR lanes of a row, the same in each of them.
 template <int LPR>
@@ -634,7 +633,7 @@ __global__ __launch_bounds__(kLazyThreads, 4) void fps_lazy_kernel(const T* src,
                 p = row_lanes_sum<LPR>(p);
                 const int j = jb + u * RPI + sub;
                 if (c == 0 && j < j1 && !(mark && key[j] == kPicked)) {
-                    key[j] = min(dev::ord_key(p * inv[j] * scale), kHighest);
+                    key[j] = dev::ord_key(p * inv[j] * scale);
                     seen[j] = mark;
                 }
             }
@@ -744,7 +743,7 @@ __global__ __launch_bounds__(kLazyThreads, 4) void fps_lazy_kernel(const T* src,
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
                     if (c16 == v && 16 * b2 + 4 * g + v < cnt) {
-                        const unsigned kk = min(~low_key[b2][v], kHighest);
+                        const unsigned kk = ~low_key[b2][v];
                         key[jo[b2][v]] = kk;
                         seen[jo[b2][v]] = (unsigned char)k;
                         atomicMin(low, ((unsigned long long)kk << 32) | (unsigned)jo[b2][v]);
@@ -756,9 +755,17 @@ __global__ __launch_bounds__(kLazyThreads, 4) void fps_lazy_kernel(const T* src,
         unsigned long long gb = ~0ull;
 #pragma unroll
         for (int w = 0; w < kLazyWaves; ++w) gb = min(gb, sh.post[w]);
-        // an unpicked row exists while k < min(m, n); the clamp only keeps
-        // the accesses below in bounds whatever the keys hold
-        const int r = min(max(__builtin_amdgcn_readfirstlane((int)(unsigned)gb), 0), n - 1);
+        // an unpicked row exists while k < min(m, n); where none has a key
+        // below the mark, NaNs are left, and the lowest of them is next
+        int r = __builtin_amdgcn_readfirstlane((int)(unsigned)gb);
+        if (gb == ~0ull) {
+            r = 0;
+            for (int i = 0; i < k; ++i)
+                if (sh.pick[i] == r) {  // each turn takes r past one pick
+                    ++r;
+                    i = -1;
+                }
+        }
         if (wave == 0) {
             if (lane < CPR) prow[k * LDP + lane] = load16(qh + (size_t)r * D + lane * EV);
             if (lane == 0) {
