@@ -1049,7 +1049,20 @@ hipError_t launch_typed(int H, int n, int kmax, const void* src, int src_rows, i
     // 119 against 128, 5000 192 against 206, 16000 691 against 617), but
     // with a head per compute unit the re-reads no longer come from L2 (512
     // heads of 1500: 114 against 170).
-    const bool lazy = sizeof(T) * D == 128 ? H >= 256 || (n >= 2048 && n <= 8192) : true;
+    // Every further pick adds to a batch's cosines, so many picks want more
+    // rows (us, lazy against stream; fp32 64: 8 heads of 1024, 128 picks 1317
+    // against 1001, of 1100 1349 against 1182, of 1500 1330 against 1356, 64
+    // picks of 1025 8 % ahead, 300 heads of 1025 with 128 11 %; fp32 128: 8
+    // heads of 1024, 128 picks 1951 against 1843, of 1025 2 % ahead, 300
+    // heads of 1100 with 128 picks 2 % behind, of 1200 6 % ahead, of 1024 with
+    // 112 39 %; bf16 64: 300 heads of 1100, 128 picks 1154 against 1069, of
+    // 1200 2 % ahead; bf16 128 is ahead throughout).
+    const int over = n - 1024;
+    const bool lazy = sizeof(T) * D == 128   ? (H >= 256 || (n >= 2048 && n <= 8192)) && over > 4 * (kmax - 88)
+                      : sizeof(T) == 2       ? true
+                      : D == 64              ? H >= 256 || over > 8 * (kmax - 64)
+                      : H >= 256             ? kmax <= 112 || over >= 128
+                                             : kmax <= 88 || over > 0;
     if (lazy && n >= 1024 && kmax <= kLazyMaxPicks && lazy_lds_bytes<T, D>(n, kmax) <= kLazyMaxLds) {
         const size_t lds = lazy_lds_bytes<T, D>(n, kmax);
         hipLaunchKernelGGL((fps_lazy_kernel<T, D>), dim3(H), dim3(kLazyThreads), lds, s, q, src_rows, n, kmax, picks, dst,
