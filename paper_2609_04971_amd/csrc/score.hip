@@ -1922,20 +1922,29 @@ hipError_t launch_score(const bkv_dims& d, const WsLayout& L, int flags, const v
                              row_lse, nullptr, ws, s);
 }
 
-// Where one launch is ahead of the three chained ones (us, one row group of
-// 144): 128 heads of 32768 tokens down to 4096 450 against 493, 64 such heads
-// 247 against 282, 128 of 16400 267 against 276.  Not ahead, so chained:
-// shorter heads, whose selection and compaction come at the end of the grid
-// with little to overlap (128 of 14000 255 against 247, of 8192 193 against
-// 150); few heads, whose selection is one workgroup each (48 of 17000 157
-// against 145, 32 of 16384 133 against 100, 8 of 16384 97 against 63; the
-// split selection serves them); evictions that keep most of the cache, whose
-// compaction wants the whole machine (28672 of 32768 tokens 1240 against
-// 1056; half of them 755 against 770); heads past 32768 tokens (the
-// selection's streaming path) and of several row groups.
+// Where one launch is ahead of the three chained ones (us, fused against
+// chained, rows of one group as given, kept tokens 1/8 unless stated):
+//   128 heads of 32768, 144 rows   446  492      64 of 32768   248  283
+//   128 of 16400                   263  270
+// Not ahead, so chained:
+//   - shorter heads, whose selection and compaction come at the end of the grid
+//     with little to overlap (144 rows: 128 of 14000 255 247, of 8192 193 150);
+//   - layers of few tokens, whose selection is one workgroup a head while the
+//     chained one splits it.  Long heads have the longer tail to overlap:
+//     fused / chained over 24 and 144 rows and 1/8 to 1/2 kept, geometric mean
+//       tokens   0.9 M   1.0 M   1.1 M   1.25 M   1.4 M   1.55 M
+//       16400    1.095   1.02    1.06    1.02     1.03    1.04
+//       18000    1.07    1.04    0.97    1.005    0.98    0.965
+//       20000    1.06    1.03    0.96    0.94     0.98    0.975
+//       25000    1.05    0.98    0.95    0.93     0.91    0.91
+//       32768    1.06    1.015   0.93    0.92     0.92    0.91
+//   - evictions that keep most of the cache, whose compaction wants the whole
+//     machine (28672 of 32768 tokens 1240 1056; at half the two are level);
+//   - heads past 32768 tokens (the selection's streaming path) and of several
+//     row groups.
 bool evict_fusable(const bkv_dims& d, const WsLayout& L) {
     return L.rtg > 0 && L.R_pad_max == L.rtg * 16 && d.N > 15360 && d.N <= 32768 &&
-           (long long)L.P * d.N >= 1500000 && 2LL * d.budget <= d.N;
+           (long long)L.P * d.N >= (d.N >= 20000 ? 1050000 : 1500000) && 2LL * d.budget <= d.N;
 }
 
 hipError_t launch_evict_fused(const bkv_dims& d, const WsLayout& L, int flags, void* K, void* V, const void* q_win,

@@ -1,7 +1,7 @@
 """How score calls are split into key chunks (host only, nothing is launched)."""
 import pytest
 
-from score_layout import CHUNK_CASES, chunk_dims, layout
+from score_layout import CHUNK_CASES, chunk_dims, fuses, layout
 import paper_2609_04971_amd as bkv
 
 
@@ -29,3 +29,13 @@ def test_chunks_cover_the_head_and_their_statistics_fit():
                     assert L.nch <= L.nch_ws or 2 * L.nch * L.R_pad_max <= N, at
                     other = layout(d, not mean)  # one workspace serves both forms
                     assert (L.evict_end, L.part_z, L.lse2) == (other.evict_end, other.part_z, other.lse2), at
+
+
+@pytest.mark.parametrize("P,N,R,budget,dtype,want", [
+    (128, 32768, 144, 4096, "bf16", True), (33, 32768, 24, 4096, "bf16", True), (32, 32768, 24, 4096, "bf16", False),
+    (53, 20000, 80, 2500, "bf16", True), (52, 20000, 80, 2500, "bf16", False), (60, 19999, 80, 2500, "bf16", False),
+    (98, 15361, 16, 2048, "bf16", True), (97, 15361, 16, 2048, "bf16", False), (256, 15360, 16, 2048, "bf16", False),
+    (128, 32769, 144, 4096, "bf16", False), (128, 32768, 145, 4096, "bf16", False), (128, 32768, 144, 16384, "bf16", True),
+    (128, 32768, 144, 16385, "bf16", False), (128, 32768, 144, 4096, "fp32", False)])
+def test_where_the_eviction_is_one_launch(P, N, R, budget, dtype, want):
+    assert fuses(bkv.dims(B=P, Hq=1, Hkv=1, D=128, N=N, W=R, C=0, budget=budget, dtype=dtype)) == want
