@@ -10,6 +10,7 @@ import pytest
 import torch
 
 from gpu_util import assert_scores_close, dims_of, raw_bits, say
+from score_layout import fuses
 import paper_2609_04971_amd as bkv
 from paper_2609_04971_amd import synth
 
@@ -69,10 +70,11 @@ def test_noalloc_options_and_internal_outputs():
 # layer on the chained calls, one on the fused launch).
 @pytest.mark.parametrize("w", [
     W("na-graph", B=2, Hq=8, Hkv=2, D=128, N=3000, W=16, C=8, budget=700, n_prefix=4, revisit_frac=0.1),
-    W("na-graph-fused", B=2, Hq=8, Hkv=2, D=128, N=16384, W=16, C=8, budget=2048, revisit_frac=0.05),
+    W("na-graph-fused", B=12, Hq=8, Hkv=8, D=128, N=16384, W=16, C=8, budget=2048, revisit_frac=0.05),
 ], ids=lambda w: w.name)
 def test_noalloc_graph_replays(w):
     d = dims_of(w)
+    assert fuses(d) == w.name.endswith("fused")
     x = synth.make_layer(w, seed=71, device="cuda")
     K0, V0 = x["K"].clone(), x["V"].clone()
     args = (x["q_win"], x["beacons"], x["counts"])
