@@ -105,9 +105,13 @@ WsLayout ws_layout(const bkv_dims& d, int flags) {
         L.key_chunk = even(n);
         // shorter chunks where that saves a nearly empty round (kChunkTail)
         const bool mean = (flags & BKV_SCORE_MEAN) != 0;
+        // not where the eviction is one launch: it takes the same chunks, its
+        // other items fill the last round, and it reads its scores back, so
+        // its statistics stay in the workspace
+        const bool choose = (mean || !multi) && !evict_fusable(d, L);
         float best = chunk_cost(d, P, L.key_chunk);
         if (!mean && L.rtg > kFewTiles) best *= kChunkMargin;
-        for (int want = 1024; want >= 768 && (mean || !multi); want -= kKeyChunkUnit) {
+        for (int want = 1024; choose && want >= 768; want -= kKeyChunkUnit) {
             const int m = (d.N + want - 1) / want, kc = even(m);
             if (m > room || kc != want || (!mean && L.rtg > kFewTiles && want < 1024)) continue;
             const float c = chunk_cost(d, P, kc);

@@ -29,6 +29,8 @@ def test_chunks_cover_the_head_and_their_statistics_fit():
                     assert L.nch <= L.nch_ws or 2 * L.nch * L.R_pad_max <= N, at
                     other = layout(d, not mean)  # one workspace serves both forms
                     assert (L.evict_end, L.part_z, L.lse2) == (other.evict_end, other.part_z, other.lse2), at
+                    # the fused launch reads its own scores back: its statistics stay in the workspace
+                    assert not (fuses(d) and other.in_scores), at
 
 
 @pytest.mark.parametrize("P,N,R,budget,dtype,want", [
