@@ -1644,13 +1644,19 @@ __global__ __launch_bounds__(kThreads, 2) void fast_score_kernel(Args a) {
 // selection workgroup of head s - lag2 and the compaction workgroups of
 // head s - lag3, in that order; the host lists the slot ranges of equal
 // size.  Workgroups that start early only wait (holding their slot), so
-// each kind comes a few machine-fulls after what it needs.
+// each kind comes a few machine-fulls after what it needs.  Consecutive
+// workgroups go to consecutive XCDs, so a slot of a multiple of 8 workgroups
+// would put every head's selection, its short last chunk and so on on one XCD
+// each; the order within a slot therefore turns so that each slot starts one
+// XCD after the one before (us without: 233 heads of 18000 to 2250, 11 + 11 +
+// 1 + 9 workgroups a slot, 493, and with 12 + 12 + 1 + 9 of them 414; 95 of
+// 16400 to 8200, 15 + 15 + 1 + 33, 343, with 13 + 13 + 1 + 33 293).
 __device__ __forceinline__ int head_of_block_fused(const Args& a, int b) {
     int i = 0;
     while (i + 1 < a.nreg && b >= a.rb[i + 1]) ++i;
-    const int per = a.rper[i];
-    const int s = a.rs[i] + (b - a.rb[i]) / per;
-    int r = (b - a.rb[i]) % per;
+    const int per = a.rper[i], slot = (b - a.rb[i]) / per;
+    const int s = a.rs[i] + slot;
+    int r = (b - a.rb[i] + slot * ((per - 1) & 7)) % per;  // each slot starts one XCD further
     if (s < a.P) {
         if (r < a.nch) return s;
         r -= a.nch;
