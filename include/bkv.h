@@ -138,6 +138,9 @@ bkv_status bkv_beacon_update(const bkv_dims* d, const void* q_new, int32_t T, fl
  * no occupied slot and W == 0 every score is -inf.
  *   row_lse optional (NULL to skip): entry c for beacon slot c (-inf when
  *           empty), entry C + g*W + w for recent query w of head h*G+g.
+ *   scores [B,Hkv,N] is written throughout.  While the call runs it may hold
+ *           row statistics, so nothing else may read or write it; after a
+ *           BKV_ERR_DEVICE its contents are unspecified.
  *   N == 0: nothing is written.  Workspace: bkv_workspace_bytes(d, SCORE). */
 bkv_status bkv_score(const bkv_dims* d, const void* K, const void* q_win, const float* beacons,
                      const int32_t* counts, const float* rope_cos, const float* rope_sin,
