@@ -1365,7 +1365,7 @@ __device__ __forceinline__ void fast_final(const Args& a, int h, int chunk, Fast
     }
     // the item's scores, kept in LDS by the key loop, go out coalesced
     const int k0 = chunk * KC, nk = min(KC, N - k0);
-    if (!a.fused) {
+    if (MULTI || !a.fused) {
         for (int i = tid; i < nk; i += kThreads) out[k0 + i] = sm.v.fin.kacc[i];
         return;
     }
@@ -1572,17 +1572,7 @@ __device__ void split_final(const Args& a, int h, int chunk, FastSmem<true>& sm,
         const unsigned u = sl.kmax[i];  // inverse of the order key
         return __uint_as_float((u & 0x80000000u) ? (u & 0x7fffffffu) : ~u) * sc;
     };
-    if (!a.fused) {
-        for (int i = tid; i < nk; i += kThreads) out[k0 + i] = score_of(i);
-        return;
-    }
-    for (int i = tid; i < nk; i += kThreads) dev::st_coherent(out + k0 + i, score_of(i));
-    dev::wait_all_memory();
-    __syncthreads();
-    if (tid == 0) {
-        int* hc = a.hctl + (size_t)h * kHcWords;
-        if (dev::fetch_add_relaxed(hc + kHcFDone, 1) == a.nch - 1) dev::st_flag(hc + kHcScReady, 1);
-    }
+    for (int i = tid; i < nk; i += kThreads) out[k0 + i] = score_of(i);
 }
 
 // S or F item of a row-split head (F items of the mean form take the
@@ -1671,9 +1661,9 @@ __device__ __forceinline__ int head_of_block_fused(const Args& a, int b) {
     return s - a.lag3;
 }
 
-template <int D, int RT, bool MULTI, bool SPLIT>
-__global__ __launch_bounds__(kThreads, 2) void evict_kernel(Args a) {
-    __shared__ FastSmem<MULTI> sm;
+template <int D, int RT>
+__global__ __launch_bounds__(kThreads, 2) void evict_kernel(Args a) {  // heads of one row group only
+    __shared__ FastSmem<false> sm;
     __shared__ StageBuf<D> sa;
     __shared__ StageBuf<D> sb;
     __shared__ int s_ticket, s_ok, s_flag;
@@ -1682,16 +1672,12 @@ __global__ __launch_bounds__(kThreads, 2) void evict_kernel(Args a) {
     if (!complete_ticket(a, req, &s_ticket, &s_ok)) return;
     const int ticket = __builtin_amdgcn_readfirstlane(s_ticket);
     if (ticket < 2 * a.nch) {
-        if constexpr (SPLIT) {
-            split_item<D, RT>(a, h, ticket, sm, sa, sb, &s_flag);
-            return;
-        }
         Op<uint16_t, D> yr[RT];
-        if (!MULTI) load_rows<D, RT>(a, h, 0, yr, threadIdx.x & 63);
+        load_rows<D, RT>(a, h, 0, yr, threadIdx.x & 63);
         if (ticket < a.nch)
-            fast_stats<D, RT, MULTI>(a, h, ticket, sm, sa, sb, yr, &s_flag);
+            fast_stats<D, RT, false>(a, h, ticket, sm, sa, sb, yr, &s_flag);
         else
-            fast_final<D, RT, MULTI>(a, h, ticket - a.nch, sm, sa, sb, yr, &s_flag);
+            fast_final<D, RT, false>(a, h, ticket - a.nch, sm, sa, sb, yr, &s_flag);
         return;
     }
     const int tid = threadIdx.x;
@@ -1748,19 +1734,13 @@ hipError_t launch_fast_rt(const Args& a, hipStream_t s) {
     const bool multi = a.R_pad_max > RT * 16;
     // four row groups of 7 to 9 tiles (R of about 400 to 576): one per wave
     if constexpr (RT >= 7) {
-        if (a.R_pad_max == kSplitGroups * RT * 16 && a.key_chunk <= kMultiKeyChunk) {
-            if (a.fused)
-                hipLaunchKernelGGL((evict_kernel<D, RT, true, true>), dim3(a.total), dim3(kThreads), 0, s, a);
-            else
-                hipLaunchKernelGGL((fast_score_kernel<D, RT, true, true>), dim3(a.total), dim3(kThreads), 0, s, a);
+        if (a.R_pad_max == kSplitGroups * RT * 16) {
+            hipLaunchKernelGGL((fast_score_kernel<D, RT, true, true>), dim3(a.total), dim3(kThreads), 0, s, a);
             return hipGetLastError();
         }
     }
     if (a.fused) {
-        if (multi)
-            hipLaunchKernelGGL((evict_kernel<D, RT, true, false>), dim3(a.total), dim3(kThreads), 0, s, a);
-        else
-            hipLaunchKernelGGL((evict_kernel<D, RT, false, false>), dim3(a.total), dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL((evict_kernel<D, RT>), dim3(a.total), dim3(kThreads), 0, s, a);
     } else if (multi) {
         hipLaunchKernelGGL((fast_score_kernel<D, RT, true, false>), dim3(a.total), dim3(kThreads), 0, s, a);
     } else {
@@ -1869,7 +1849,9 @@ hipError_t launch_score_impl(const bkv_dims& d, const WsLayout& L, int flags, co
     // (two resident workgroups per CU).  The F items, whose key loads are
     // non-temporal, then find their head's normalisers ready more often
     // while the re-read still comes from the memory-side cache: on the 32K
-    // layer lags of 14 to 24 heads scored about 4 % faster than 8 and 32.
+    // layer in 32 chunks a head lags of 14 to 24 heads scored about 4 % faster
+    // than 8 and 32 (16 was taken; with its 20 chunks now it is 26, the same
+    // work ahead).
     int dev_id = 0, cus = 256;
     if (hipGetDevice(&dev_id) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev_id) != hipSuccess)
@@ -1939,11 +1921,11 @@ hipError_t launch_score(const bkv_dims& d, const WsLayout& L, int flags, const v
 //     chained one splits it.  Long heads have the longer tail to overlap:
 //     fused / chained over 24 and 144 rows and 1/8 to 1/2 kept, geometric mean
 //       tokens   0.9 M   1.0 M   1.1 M   1.25 M   1.4 M   1.55 M
-//       16400    1.095   1.02    1.06    1.02     1.03    1.04
-//       18000    1.07    1.04    0.97    1.005    0.98    0.965
-//       20000    1.06    1.03    0.96    0.94     0.98    0.975
-//       25000    1.05    0.98    0.95    0.93     0.91    0.91
-//       32768    1.06    1.015   0.93    0.92     0.92    0.91
+//       16400    1.11    1.02    1.06    1.02     1.01    0.99
+//       18000    1.08    1.05    0.97    1.00     0.98    0.97
+//       20000    1.09    1.05    0.98    0.955    1.00    0.99
+//       25000    1.06    0.995   0.96    0.93     0.92    0.92
+//       32768    1.08    1.03    0.95    0.93     0.94    0.92
 //   - evictions that keep most of the cache, whose compaction wants the whole
 //     machine (28672 of 32768 tokens 1240 1056; at half the two are level);
 //   - heads past 32768 tokens (the selection's streaming path) and of several
