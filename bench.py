@@ -202,7 +202,7 @@ def main():
     evict_med = statistics.median(evict_us)
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": measured_traffic(),
-                "kernel": "eviction launch: rows_kernel<128> + evict_kernel<128, 9, false, false>",
+                "kernel": "eviction launch: rows_kernel<128> + evict_kernel<128, 9>",
                 "algorithmic_bytes": evict_bytes, "moved_rows": moved,
                 "launch_us_mean": round(avg_us["evict"], 1),
                 "mfma_tflops": round(evict_flops / evict_s / 1e12, 1),
