@@ -1044,11 +1044,21 @@ hipError_t launch_typed(int H, int n, int kmax, const void* src, int src_rows, i
     // 512 bytes (8 fp32 heads of 1024 x 64: 131 against 149 us; 8 bf16 heads
     // of 1100 x 128: 117 against 198; 16384 rows: 983 against 2203).  Below
     // 1024 fp32 rows a wave has too few rows per step (32 heads of 300 x 64:
-    // 99 against 58).  Rows of 128 bytes are cheap to re-read: 8 heads gain
-    // between 2048 and 8192 rows only (m = 8: 2000 rows 91 against 89, 3000
+    // 99 against 58).  Rows of 128 bytes are cheap to re-read: few heads
+    // gain between 2048 and 8192 rows only (8 heads, any rows, m = 8: 2000 rows 91 against 89, 3000
     // 119 against 128, 5000 192 against 206, 16000 691 against 617), but
     // with a head per compute unit the re-reads no longer come from L2 (512
-    // heads of 1500: 114 against 170).
+    // heads of 1500: 114 against 170).  What is read again depends on the
+    // rows: in tight clusters one pick raises many S_j.  Few heads of 128-byte
+    // rows have too little to win that back by: two picks need nothing read
+    // again, and from 14 on clusters gain or lose a little, but between them
+    // more is lost than given (stream's time over lazy's, 2 / 6 / 10 / 14 / 20
+    // picks, 32 heads of 4096: queries about a few directions as synth.py
+    // makes them 1.84 0.99 1.09 1.24 1.36, 8 clusters of the same spread 1.85
+    // 0.95 0.89 1.04 1.23, of a tenth of it 1.84 0.64 0.72 0.87 1.05).
+    // Elsewhere tight clusters lose 5 % at most (4 to 8 picks of few fp32 heads
+    // of 64, or of 512 bf16 ones); sets of 8 distinct rows up to 32 % with 4 to
+    // 8 picks and up to 6 % with 16.
     // Every further pick adds to a batch's cosines, so many picks want more
     // rows (us, lazy against stream; fp32 64: 8 heads of 1024, 128 picks 1317
     // against 1001, of 1100 1349 against 1182, of 1500 1330 against 1356, 64
@@ -1058,7 +1068,8 @@ hipError_t launch_typed(int H, int n, int kmax, const void* src, int src_rows, i
     // 112 39 %; bf16 64: 300 heads of 1100, 128 picks 1154 against 1069, of
     // 1200 2 % ahead; bf16 128 is ahead throughout).
     const int over = n - 1024;
-    const bool lazy = sizeof(T) * D == 128   ? (H >= 256 || (n >= 2048 && n <= 8192)) && over > 4 * (kmax - 88)
+    const bool pays = H >= 256 || (n >= 2048 && n <= 8192 && (kmax <= 2 || kmax >= 14));
+    const bool lazy = sizeof(T) * D == 128   ? pays && over > 4 * (kmax - 88)
                       : sizeof(T) == 2       ? true
                       : D == 64              ? H >= 256 || over > 8 * (kmax - 64)
                       : H >= 256             ? kmax <= 112 || over >= 128

@@ -158,13 +158,14 @@ def test_fps_large_sets(dtype, D, n, m, H):
 # The lazy kernel (rows brought up to date only where they can be the
 # argmin): its smallest sets, ragged ones, batches and pick tiles of 16 and
 # 32 crossed, one pick, the most picks it takes (128) and one more, 128-byte
-# rows with few and with many heads, and both sides of the rows that many
-# picks want.
+# rows with few and with many heads, both sides of the rows that many picks
+# want and of the picks that few heads of such rows want.
 LAZY_CASES = [("fp32", 64, 1024, 16, 3), ("fp32", 128, 1027, 34, 2), ("bf16", 128, 1025, 1, 2), ("bf16", 128, 1031, 2, 3),
               ("bf16", 128, 1500, 128, 2), ("bf16", 128, 1500, 129, 1), ("bf16", 128, 4096, 17, 2),
               ("fp32", 64, 1100, 128, 2), ("fp32", 64, 1537, 128, 2), ("fp32", 128, 1024, 100, 2), ("fp32", 128, 1152, 120, 257),
               ("bf16", 64, 1104, 108, 256), ("bf16", 64, 1105, 108, 256),
-              ("bf16", 64, 2048, 33, 2), ("bf16", 64, 1030, 16, 256), ("fp32", 128, 3001, 16, 1)]
+              ("bf16", 64, 2048, 33, 2), ("bf16", 64, 1030, 16, 256), ("fp32", 128, 3001, 16, 1),
+              ("bf16", 64, 2048, 2, 2), ("bf16", 64, 2049, 3, 2), ("bf16", 64, 2049, 13, 2), ("bf16", 64, 2049, 14, 2)]
 
 
 @pytest.mark.parametrize("dtype,D,n,m,H", LAZY_CASES)
